@@ -75,6 +75,143 @@ __device__ __forceinline__ double sum_squares(const float (&v)[NV])
     return ss;
 }
 
+// A row's norm, and its reciprocal as a pair of floats (inv + inv_lo is 1 / norm
+// to about 2^-48).  v * inv in float lies within two float ulps of the exact
+// quotient (one rounding of inv, one of the product), so wherever that product
+// is further than that from a rounding boundary of the stored format, both
+// round to the same stored value.  The few values closer than twice that,
+// about one in 8,000, are settled by the product's residual (to about 2^-45
+// of the quotient), and what that leaves open, like rows of extreme norm, by
+// the division and rounding in double that define the result.
+struct RowScale {
+    double norm;
+    float inv, inv_lo;
+    bool fast;
+};
+
+__device__ __forceinline__ RowScale row_scale(double norm)
+{
+    RowScale s;
+    s.norm = norm;
+    s.fast = norm >= 0x1p-60 && norm <= 0x1p60;  // inv and the products of ordinary values stay normal
+    const double full = s.fast ? 1.0 / norm : 0.0;
+    s.inv = (float)full;
+    s.inv_lo = (float)(full - (double)s.inv);
+    return s;
+}
+
+// What v / norm exceeds the float product q = v * inv by, to about 2^-45 of it.
+__device__ __forceinline__ float quotient_rest(float v, float q, const RowScale& s)
+{
+    return fmaf(v, s.inv, -q) + v * s.inv_lo;
+}
+
+// Whether the quotient q is too close to the middle of two bf16 values (or
+// too small a number) for its float bits to decide the rounding.
+__device__ __forceinline__ bool bf16_near(float q)
+{
+    const uint32_t u = __float_as_uint(q);
+    return ((u - 0x7FFCu) & 0xFFFFu) <= 8u || (u << 1) - 1u < (54u << 24);
+}
+
+// The bf16 value that v / norm rounds to, for q = v * inv with bf16_near(q).
+__device__ __forceinline__ uint16_t bf16_settle(float v, float q, const RowScale& s)
+{
+    const uint32_t u = __float_as_uint(q);
+    const float mid = __uint_as_float((u & 0xFFFF0000u) | 0x8000u);
+    const float above = (q - mid) + quotient_rest(v, q, s);  // q - mid is a few ulps: exact
+    if (!s.fast || (u << 1) - 1u < (54u << 24) || !(fabsf(above) > fabsf(q) * 0x1p-40f))
+        return double_to_bf16_rne((double)v / s.norm);
+    return (uint16_t)((u >> 16) + ((above > 0.f) != (q < 0.f) ? 1u : 0u));
+}
+
+__device__ __forceinline__ uint16_t unit_bf16(float v, const RowScale& s)
+{
+    const float q = v * s.inv;
+    if (!s.fast || bf16_near(q))
+        return bf16_settle(v, q, s);
+    return (uint16_t)((__float_as_uint(q) + 0x8000u) >> 16);
+}
+
+// Eight columns c .. c + 7 of the raw row that starts at element `at` (d
+// columns; those past it read as zeros), in 16-byte pieces: one of bf16 or two
+// of f32 values.  VEC: every piece of a row is 16-byte aligned (base and row
+// stride), so it lies inside the row or past it whole; else element loads.
+template <bool F32, bool VEC>
+__device__ __forceinline__ void load_chunk(const void* __restrict__ raw, int64_t at, int32_t c, int32_t d,
+                                           u32x4 (&x)[F32 ? 2 : 1])
+{
+    constexpr int P = F32 ? 2 : 1;  // pieces
+#pragma unroll
+    for (int p = 0; p < P; p++) {
+        const int32_t c0 = c + p * (8 / P);
+        if constexpr (VEC) {
+            x[p] = *(const u32x4*)((const char*)raw + (at + (c0 < d ? c0 : 0)) * (F32 ? 4 : 2));
+            if (c0 >= d)
+                x[p] = u32x4{0, 0, 0, 0};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                if constexpr (F32) {
+                    const uint32_t v = ((const uint32_t*)raw)[at + (c0 + e < d ? c0 + e : 0)];
+                    x[p][e] = c0 + e < d ? v : 0u;
+                } else {
+                    const int32_t ca = c0 + 2 * e, cb = ca + 1;
+                    const uint32_t lo = ((const uint16_t*)raw)[at + (ca < d ? ca : 0)];
+                    const uint32_t hi = ((const uint16_t*)raw)[at + (cb < d ? cb : 0)];
+                    x[p][e] = (ca < d ? lo : 0u) | (cb < d ? hi << 16 : 0u);
+                }
+            }
+        }
+    }
+}
+
+// Column e of a chunk.
+template <bool F32>
+__device__ __forceinline__ float chunk_value(const u32x4 (&x)[F32 ? 2 : 1], int e)
+{
+    if constexpr (F32)
+        return __uint_as_float(x[e >> 2][e & 3]);
+    else
+        return __uint_as_float((e & 1) ? x[0][e >> 1] & 0xFFFF0000u : x[0][e >> 1] << 16);
+}
+
+// A chunk's eight bf16 values of the unit row (zeros for a zero or NaN row).
+template <bool F32>
+__device__ __forceinline__ u32x4 unit_chunk_bf16(const u32x4 (&x)[F32 ? 2 : 1], const RowScale& sc)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    u32x4 w;
+    bool near = !sc.fast;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const float q0 = chunk_value<F32>(x, e) * sc.inv, q1 = chunk_value<F32>(x, e + 1) * sc.inv;
+        near |= bf16_near(q0) || bf16_near(q1);
+        w[e >> 1] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)q0, (__bf16)q1});
+    }
+    const bool some = sc.norm > 0.0;
+    if (near && some) {  // rare: some value of this chunk is not decided yet
+        uint32_t open = 0;
+#pragma unroll
+        for (int e = 0; e < 8; e++)
+            open |= (!sc.fast || bf16_near(chunk_value<F32>(x, e) * sc.inv)) ? 1u << e : 0u;
+        while (open) {
+            const int at_e = __ffs((int)open) - 1;
+            open &= open - 1;
+            float v = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                v = e == at_e ? chunk_value<F32>(x, e) : v;
+            const uint32_t bits = bf16_settle(v, v * sc.inv, sc);
+            const int pos = (at_e & 1) * 16;
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                w[q] = q == (at_e >> 1) ? (w[q] & ~(0xFFFFu << pos)) | (bits << pos) : w[q];
+        }
+    }
+    return some ? w : u32x4{0, 0, 0, 0};
+}
+
 // normalize_row for ld <= NT * NV: the row is read once into registers.
 template <int NT, int NV, class Dst>
 __device__ __forceinline__ void normalize_row_regs(const void* raw, int dtype, int64_t row, int32_t d,
@@ -83,12 +220,12 @@ __device__ __forceinline__ void normalize_row_regs(const void* raw, int dtype, i
     const int t = threadIdx.x;
     float v[NV];
     load_row<NT, NV>(raw, dtype, row, d, live, v);
-    const double norm = sqrt(block_sum<NT>(sum_squares(v), red));
+    const RowScale sc = row_scale(sqrt(block_sum<NT>(sum_squares(v), red)));
 #pragma unroll
     for (int i = 0; i < NV; i++) {
         const int32_t j = i * NT + t;
         if (j < ld)
-            dst(j, (j < d && norm > 0.0) ? double_to_bf16_rne((double)v[i] / norm) : (uint16_t)0);
+            dst(j, (j < d && sc.norm > 0.0) ? unit_bf16(v[i], sc) : (uint16_t)0);
     }
 }
 

@@ -3,12 +3,15 @@
 // precision; queries get the same treatment so that the dot product of the
 // two operands is their cosine, Algorithm 1 retrieve step).
 //
-// One 1024-thread block per row (a row of up to 8192 columns is read once,
-// at most eight values per thread: with fewer threads the double division
-// and rounding of each value, not memory, set the time of a small call).  The
-// squared norm is accumulated in double with a fixed reduction tree, so
-// identical raw rows always produce identical stored bits wherever they sit
-// in the pool.
+// Small calls (queries, the positions of a step): one 1024-thread block per
+// row (a row of up to 8192 columns is read once, at most eight values per
+// thread: the latency of one row's work, not memory, sets the time).  Bulk
+// appends: store_rows_kernel, eight rows per workgroup.  The squared norm is
+// accumulated in double, each quotient by it rounded once (RowScale: nearly
+// all of them without a division), so identical raw rows always produce
+// identical stored bits wherever they sit in the pool.
+#include <type_traits>
+
 #include "common.hpp"
 #include "internal.hpp"
 #include "rowops.hpp"
@@ -59,24 +62,6 @@ __global__ __launch_bounds__(kRowThreads) void normalize_rows_kernel(
     }
 }
 
-hipError_t launch_normalize_rows(const void* raw, int dtype, int32_t d, int64_t n_rows_in,
-                                 int64_t n_rows_out, uint16_t* out, int64_t row_offset, int32_t ld,
-                                 int layout, int64_t rs, int64_t ws, const int32_t* tok_in,
-                                 const int32_t* trace_in, const int32_t* prompt_in, int32_t* tok_out,
-                                 int32_t* trace_out, int32_t* prompt_out, hipStream_t stream)
-{
-    if (n_rows_out <= 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(normalize_rows_kernel, dim3((unsigned)n_rows_out), dim3(kRowThreads), 0, stream, raw,
-                       dtype, d, n_rows_in, out, row_offset, ld, layout, rs, ws, tok_in, trace_in,
-                       prompt_in, tok_out, trace_out, prompt_out);
-    return hipGetLastError();
-}
-
-}  // namespace oil
-
-namespace oil {
-
 // Nearest OCP E4M3 code of v (|v| <= 448: larger magnitudes saturate to
 // 448), ties to the even code.  The representable magnitudes are multiples of
 // 2^(E - 3) in [2^E, 2^(E + 1)) for E >= -6 and of 2^-9 below 2^-6; scaling by
@@ -96,6 +81,58 @@ __device__ __forceinline__ uint8_t double_to_e4m3_rne(double v)
         return (uint8_t)(sign | (uint8_t)(((E + 7) << 3) + (int)r - 8));
     }
     return (uint8_t)(sign | (uint8_t)rint(ldexp(a, 9)));
+}
+
+// |q| in multiples of the spacing of E4M3 codes around it (exact; in [0, 16]),
+// and what to add to the rounded multiple for the code of that binade.
+__device__ __forceinline__ float e4m3_steps(float q, float& scale, int& base)
+{
+    const int E = max((int)((__float_as_uint(q) >> 23) & 255u), 127 - 6);  // biased exponent, at least that of 2^-6
+    scale = __uint_as_float((uint32_t)(127 + 127 + 3 - E) << 23);
+    base = ((E - 120) << 3) - 8;
+    return fabsf(q) * scale;
+}
+
+// Whether the scaled quotient q is too close to the middle of two E4M3 codes
+// for its float bits to decide the rounding: within four ulps of a middle, or
+// below 2^-6, where the codes' spacing no longer follows q's exponent (about
+// one value in 4,000 of a Gaussian row).
+__device__ __forceinline__ bool e4m3_near(float q)
+{
+    const uint32_t u = __float_as_uint(q);
+    return ((u - 0x7FFFCu) & 0xFFFFFu) <= 8u || (u << 1) - 1u < 2u * 0x3C800000u - 1u;
+}
+
+// The code that the scaled quotient v / norm * 2^shift rounds to, for q =
+// v * s.inv with s already scaled by 2^shift (its norm is not) and a near
+// number of steps.
+__device__ __forceinline__ uint8_t e4m3_settle(float v, float q, const RowScale& s, int shift)
+{
+    float scale;
+    int base;
+    const float a = e4m3_steps(q, scale, base), low = floorf(a);
+    const float rest = quotient_rest(v, q, s) * scale;
+    const float above = (a - (low + 0.5f)) + (q < 0.f ? -rest : rest);
+    if (!s.fast || !(fabsf(above) > a * 0x1p-40f))
+        return double_to_e4m3_rne(ldexp((double)v / s.norm, shift));
+    return (uint8_t)(((__float_as_uint(q) >> 24) & 0x80u) |
+                     (uint32_t)(base + (int)low + (above > 0.f ? 1 : 0)));
+}
+
+// s scaled for fp8 rows: inv and inv_lo times 2^shift (exact).
+__device__ __forceinline__ RowScale scaled(RowScale s, int shift)
+{
+    s.inv = ldexpf(s.inv, shift);
+    s.inv_lo = ldexpf(s.inv_lo, shift);
+    return s;
+}
+
+__device__ __forceinline__ uint8_t unit_e4m3(float v, const RowScale& s, int shift)
+{
+    const float q = v * s.inv;
+    if (!s.fast || e4m3_near(q))
+        return e4m3_settle(v, q, s, shift);
+    return (uint8_t)__builtin_amdgcn_cvt_pk_fp8_f32(q, q, 0, false);
 }
 
 // fp8 tile layout (bytes): rows in blocks of 32, columns in windows of 128;
@@ -143,19 +180,19 @@ __device__ __forceinline__ int quantize_row_regs(const void* raw, int dtype, int
     const int t = threadIdx.x;
     float v[NV];
     load_row<NT, NV>(raw, dtype, r, d, live, v);
-    const double norm = sqrt(block_sum<NT>(sum_squares(v), red));
-    double m = 0.0;
-    if (norm > 0.0) {
+    const RowScale sc = row_scale(sqrt(block_sum<NT>(sum_squares(v), red)));
+    // division is monotonic: the largest quotient is the largest value's
+    float top = 0.f;
 #pragma unroll
-        for (int i = 0; i < NV; i++)
-            m = fmax(m, fabs((double)v[i] / norm));
-    }
-    const int shift = fp8_shift(block_max<NT>(m, red));
+    for (int i = 0; i < NV; i++)
+        top = fmaxf(top, fabsf(v[i]));
+    const int shift = fp8_shift(block_max<NT>(sc.norm > 0.0 ? (double)top / sc.norm : 0.0, red));
+    const RowScale s8 = scaled(sc, shift);
 #pragma unroll
     for (int i = 0; i < NV; i++) {
         const int32_t j = i * NT + t;
         if (j < ld8)
-            dst(j, (j < d && norm > 0.0) ? double_to_e4m3_rne(ldexp((double)v[i] / norm, shift)) : (uint8_t)0);
+            dst(j, (j < d && sc.norm > 0.0) ? unit_e4m3(v[i], s8, shift) : (uint8_t)0);
     }
     return shift;
 }
@@ -213,6 +250,225 @@ __global__ __launch_bounds__(kRowThreads) void quantize_rows_kernel(
     }
 }
 
+// ----------------------------------------------------------------- bulk appends
+// One 512-thread workgroup per R = 8 (or 4) stored rows, aligned to R, so they
+// share a 32-row block.  Lane l of a wave holds row l % R; the 64 / R lanes of
+// a row take neighbouring 8-column chunks (fp8: 16 columns), so a wave's loads
+// read contiguous stretches of each row and its stores write 16 bytes per
+// lane, 16 R contiguous bytes of the tile per R rows.  (One workgroup per row
+// stored two bytes per thread, scattered over the tiles, and rounded every
+// value through a division in double.)
+// The rows stay in registers between the norm and the rounding: memory is
+// read once and written once, which is what bounds it: 60,001 rows of 4,096
+// bf16 values into a bf16 pool 896 -> 201 us (4.9 TB/s in and out, a plain
+// copy's rate), 20,011 rows of 5,120 f32 values into an fp8 pool 331 -> 130.
+//
+// VEC: whole 16-byte pieces of every row are aligned (base and row stride);
+// other widths load element by element.
+constexpr int kBulkThreads = 512;
+
+// The 16 codes of two chunks of a unit row scaled by 2^shift (s is scaled; zeros
+// for a zero or NaN row).
+template <bool F32>
+__device__ __forceinline__ u32x4 unit_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1], const RowScale& s, int shift)
+{
+    u32x4 w = {0, 0, 0, 0};
+    auto quotient = [&](int e) { return chunk_value<F32>(x[e >> 3], e & 7) * s.inv; };
+    bool near = !s.fast;
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+        const float q0 = quotient(e), q1 = quotient(e + 1);
+        near |= e4m3_near(q0) || e4m3_near(q1);
+        if (e & 2)
+            w[e >> 2] = __builtin_amdgcn_cvt_pk_fp8_f32(q0, q1, w[e >> 2], true);
+        else
+            w[e >> 2] = __builtin_amdgcn_cvt_pk_fp8_f32(q0, q1, w[e >> 2], false);
+    }
+    const bool some = s.norm > 0.0;
+    if (near && some) {  // rare: some value of the two chunks is not decided yet
+        uint32_t open = 0;
+#pragma unroll
+        for (int e = 0; e < 16; e++)
+            open |= (!s.fast || e4m3_near(quotient(e))) ? 1u << e : 0u;
+        while (open) {
+            const int at_e = __ffs((int)open) - 1;
+            open &= open - 1;
+            float v = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; e++)
+                v = e == at_e ? chunk_value<F32>(x[e >> 3], e & 7) : v;
+            const uint32_t bits = e4m3_settle(v, v * s.inv, s, shift);
+            const int pos = (at_e & 3) * 8;
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                w[q] = q == (at_e >> 2) ? (w[q] & ~(0xFFu << pos)) | (bits << pos) : w[q];
+        }
+    }
+    return some ? w : u32x4{0, 0, 0, 0};
+}
+
+template <int FMT, bool F32, bool VEC, int NI, int R>
+__global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4))) void store_rows_kernel(
+    const void* __restrict__ raw, int32_t d, int64_t n, uint8_t* __restrict__ out, int64_t row_offset, int32_t ld,
+    int64_t rs, int64_t ws, float* __restrict__ inv_scale, const int32_t* __restrict__ tok_in,
+    const int32_t* __restrict__ trace_in, const int32_t* __restrict__ prompt_in, int32_t* __restrict__ tok_out,
+    int32_t* __restrict__ trace_out, int32_t* __restrict__ prompt_out)
+{
+    constexpr int H = FMT == kKeyFp8 ? 2 : 1;  // 8-column chunks per unit
+    constexpr int kUnits = kBulkThreads / R;     // units of a row per iteration
+    __shared__ double red[kBulkThreads / 64][R];
+    __shared__ float redm[kBulkThreads / 64][R];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane & (R - 1);
+    const int u0 = wave * (64 / R) + lane / R;
+    const int64_t dst = (row_offset / R + blockIdx.x) * R + r;
+    const int64_t src = dst - row_offset;
+    const bool live = src >= 0 && src < n;
+    const int64_t at = (live ? src : 0) * d;  // rows outside the call read row 0 and store nothing
+    const int units = ld / (8 * H);
+    // first column of chunk h of unit u
+    auto col_of = [&](int u, int h) -> int32_t {
+        if constexpr (FMT == kKeyFp8)
+            return (u >> 3) * 128 + ((u & 7) >> 1) * 32 + (u & 1) * 8 + h * 16;
+        else
+            return u * 8;
+    };
+    u32x4 x[NI][H][F32 ? 2 : 1];
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+#pragma unroll
+        for (int h = 0; h < H; h++)
+            load_chunk<F32, VEC>(raw, at, col_of(u0 + i * kUnits, h), d, x[i][h]);
+    auto value = [&](int i, int h, int e) { return chunk_value<F32>(x[i][h], e); };
+    double ss = 0.0;
+    float top = 0.f;
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+#pragma unroll
+        for (int h = 0; h < H; h++)
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const float v = value(i, h, e);
+                const double vd = v;
+                ss += vd * vd;
+                if constexpr (FMT == kKeyFp8)
+                    top = fmaxf(top, fabsf(v));
+            }
+#pragma unroll
+    for (int o = 32; o >= R; o >>= 1) {
+        ss += __shfl_xor(ss, o, kWave);
+        if constexpr (FMT == kKeyFp8)
+            top = fmaxf(top, __shfl_xor(top, o, kWave));
+    }
+    if (lane < R) {
+        red[wave][lane] = ss;
+        if constexpr (FMT == kKeyFp8)
+            redm[wave][lane] = top;
+    }
+    __syncthreads();
+    ss = 0.0;
+#pragma unroll
+    for (int w = 0; w < kBulkThreads / 64; w++) {
+        ss += red[w][r];
+        if constexpr (FMT == kKeyFp8)
+            top = fmaxf(top, redm[w][r]);
+    }
+    if (!live)
+        return;
+    if constexpr (!F32) {
+        // unpacked again below: the floats of the norm would otherwise stay in
+        // registers beside the raw pieces (half the workgroups in flight)
+#pragma unroll
+        for (int i = 0; i < NI; i++)
+#pragma unroll
+            for (int h = 0; h < H; h++)
+                asm volatile("" : "+v"(x[i][h][0]));
+    }
+    RowScale sc = row_scale(sqrt(ss));
+    int shift = 0;
+    if constexpr (FMT == kKeyFp8) {
+        shift = fp8_shift(sc.norm > 0.0 ? (double)top / sc.norm : 0.0);
+        sc = scaled(sc, shift);
+    }
+    uint8_t* base = out + (dst >> 5) * rs;
+    const int row32 = (int)(dst & 31);
+#pragma unroll
+    for (int i = 0; i < NI; i++) {
+        const int u = u0 + i * kUnits;
+        if (u >= units)
+            break;
+        u32x4 w;  // the unit's 16 stored bytes
+        if constexpr (FMT == kKeyFp8)
+            w = unit_e4m3_16<F32>(x[i], sc, shift);
+        else
+            w = unit_chunk_bf16<F32>(x[i][0], sc);
+        // 16-byte slot of (row, unit) in its 4 KiB tile
+        const int slot = FMT == kKeyFp8 ? ((u & 7) >> 1) * 64 + row32 + 32 * (u & 1)
+                                        : (u & 3) * 64 + row32 + 32 * ((u & 7) >> 2);
+        *(u32x4*)(base + (int64_t)(u >> 3) * ws + slot * 16) = w;
+    }
+    if (u0 == 0) {  // one lane per row
+        if constexpr (FMT == kKeyFp8)
+            inv_scale[dst] = ldexpf(1.f, -shift);
+        tok_out[dst] = tok_in[src];
+        trace_out[dst] = trace_in[src];
+        if (prompt_out)
+            prompt_out[dst] = prompt_in[src];
+    }
+}
+
+// Rows from which a call into tiles takes store_rows_kernel: below, a
+// 1024-thread workgroup per row fills the chip sooner (512 rows of 8,192 bf16
+// columns 16.6 us against 18.3; 768 rows 22.8 against 19.1, 2,048 rows of
+// 4,096 31 against 14).
+#ifndef OIL_BULK_MIN
+#define OIL_BULK_MIN 640
+#endif
+static bool bulk_rows(int64_t n, int32_t ld) { return n >= OIL_BULK_MIN && ld <= 8192; }
+
+// rs, ws: tile strides in bytes.
+template <int FMT>
+static hipError_t launch_store_rows(const void* raw, int dtype, int32_t d, int64_t n, uint8_t* out,
+                                    int64_t row_offset, int32_t ld, int64_t rs, int64_t ws, float* inv_scale,
+                                    const int32_t* tok_in, const int32_t* trace_in, const int32_t* prompt_in,
+                                    int32_t* tok_out, int32_t* trace_out, int32_t* prompt_out, hipStream_t stream)
+{
+    const int ni = (ld + (FMT == kKeyFp8 ? 1024 : 512) - 1) / (FMT == kKeyFp8 ? 1024 : 512);  // 8 rows per workgroup
+    const bool vec = ((int64_t)d * (dtype == 0 ? 4 : 2)) % 16 == 0;
+    // NI iterations hold R rows, so that two workgroups fit a compute unit (one
+    // loads while the other rounds): past 64 to 80 registers of raw values per
+    // thread, four rows to a workgroup.  20,000 rows, us, 8 against 4 rows:
+    // f32 to fp8 5,120 / 8,192 wide 145 / 231 against 130 / 172; bf16 to fp8
+    // 69 / 149 against 85 / 118; f32 to bf16 127 / 220 against 143 / 216; bf16
+    // to bf16 8,192 wide 143 against 168.
+    auto go = [&](auto kernel, int R) {
+        const int64_t groups = (row_offset + n - 1) / R - row_offset / R + 1;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(kBulkThreads), 0, stream, raw, d, n, out, row_offset,
+                           ld, rs, ws, inv_scale, tok_in, trace_in, prompt_in, tok_out, trace_out, prompt_out);
+    };
+    auto by_width = [&](auto f32, auto v) {
+        constexpr bool F = decltype(f32)::value, V = decltype(v)::value;
+        if constexpr (FMT == kKeyFp8) {
+            if (V && ni <= 2) go(store_rows_kernel<FMT, F, V, V ? 2 : 4, 8>, 8);
+            else if (ni <= 4) go(store_rows_kernel<FMT, F, V, 4, 8>, 8);
+            else if (V && !F && ni <= 5) go(store_rows_kernel<FMT, F, V, V && !F ? 5 : 4, V && !F ? 8 : 4>, 8);
+            else if (V && ni <= 6) go(store_rows_kernel<FMT, F, V, V ? 3 : 4, 4>, 4);
+            else go(store_rows_kernel<FMT, F, V, 4, 4>, 4);
+        } else {
+            if (V && ni <= 4) go(store_rows_kernel<FMT, F, V, V ? 4 : 8, 8>, 8);
+            else if (ni <= 8) go(store_rows_kernel<FMT, F, V, 8, 8>, 8);
+            else if (V && ni <= 10) go(store_rows_kernel<FMT, F, V, V ? 10 : 8, V ? 8 : 4>, 8);
+            else if (V && !F) go(store_rows_kernel<FMT, F, V, V && !F ? 16 : 8, V && !F ? 8 : 4>, 8);
+            else go(store_rows_kernel<FMT, F, V, 8, 4>, 4);
+        }
+    };
+    if (dtype == 0)
+        vec ? by_width(std::true_type{}, std::true_type{}) : by_width(std::true_type{}, std::false_type{});
+    else
+        vec ? by_width(std::false_type{}, std::true_type{}) : by_width(std::false_type{}, std::false_type{});
+    return hipGetLastError();
+}
+
 hipError_t launch_quantize_rows(const void* raw, int dtype, int32_t d, int64_t n_rows_in, int64_t n_rows_out,
                                 uint8_t* out, int64_t row_offset, int32_t ld8, int64_t rs_bytes,
                                 int64_t ws_bytes, float* inv_scale, const int32_t* tok_in,
@@ -221,8 +477,30 @@ hipError_t launch_quantize_rows(const void* raw, int dtype, int32_t d, int64_t n
 {
     if (n_rows_out <= 0)
         return hipSuccess;
+    if (tok_out && rs_bytes > 0 && n_rows_in == n_rows_out && bulk_rows(n_rows_in, ld8))
+        return launch_store_rows<kKeyFp8>(raw, dtype, d, n_rows_in, out, row_offset, ld8, rs_bytes, ws_bytes,
+                                          inv_scale, tok_in, trace_in, prompt_in, tok_out, trace_out, prompt_out,
+                                          stream);
     hipLaunchKernelGGL(quantize_rows_kernel, dim3((unsigned)n_rows_out), dim3(kRowThreads), 0, stream, raw, dtype, d,
                        n_rows_in, out, row_offset, ld8, rs_bytes, ws_bytes, inv_scale, tok_in, trace_in,
+                       prompt_in, tok_out, trace_out, prompt_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_normalize_rows(const void* raw, int dtype, int32_t d, int64_t n_rows_in,
+                                 int64_t n_rows_out, uint16_t* out, int64_t row_offset, int32_t ld,
+                                 int layout, int64_t rs, int64_t ws, const int32_t* tok_in,
+                                 const int32_t* trace_in, const int32_t* prompt_in, int32_t* tok_out,
+                                 int32_t* trace_out, int32_t* prompt_out, hipStream_t stream)
+{
+    if (n_rows_out <= 0)
+        return hipSuccess;
+    if (tok_out && layout == kLayoutTiled && n_rows_in == n_rows_out && bulk_rows(n_rows_in, ld))
+        return launch_store_rows<kKeyBf16>(raw, dtype, d, n_rows_in, (uint8_t*)out, row_offset, ld, 2 * rs, 2 * ws,
+                                           nullptr, tok_in, trace_in, prompt_in, tok_out, trace_out, prompt_out,
+                                           stream);
+    hipLaunchKernelGGL(normalize_rows_kernel, dim3((unsigned)n_rows_out), dim3(kRowThreads), 0, stream, raw,
+                       dtype, d, n_rows_in, out, row_offset, ld, layout, rs, ws, tok_in, trace_in,
                        prompt_in, tok_out, trace_out, prompt_out);
     return hipGetLastError();
 }

@@ -11,7 +11,8 @@ import torch
 
 import oracle
 import workloads
-from tests._parity import TOL, away_from_edges, check_topk, fp32_bound, oracle_rows, untile_keys
+from tests._parity import (TOL, away_from_edges, check_topk, fp32_bound, oracle_rows, untile_keys,
+                           untile_keys_fp8)
 
 pytestmark = pytest.mark.gpu
 
@@ -73,6 +74,62 @@ def test_store_matches_oracle(oil, d, dtype):
     assert torch.equal(pool.tokens[:n].cpu(), wp.tokens)
     assert torch.equal(pool.traces[:n].cpu(), wp.traces)
     assert torch.equal(pool.prompts[:n].cpu(), wp.prompts)
+
+
+def _four_squares(m):
+    """a, b, c, e with a^2 + b^2 + c^2 + e^2 = m."""
+    for e in range(4):
+        for a in range(int((m - e * e) ** 0.5), 0, -1):
+            for b in range(int((m - e * e - a * a) ** 0.5), -1, -1):
+                c = int(round((m - e * e - a * a - b * b) ** 0.5))
+                if a * a + b * b + c * c + e * e == m:
+                    return a, b, c, e
+    raise ValueError(m)
+
+
+@pytest.mark.parametrize("key_format", ["bf16", "fp8"])
+@pytest.mark.parametrize("n,d,dtype", [(639, 4096, "bf16"), (640, 4096, "bf16"), (777, 512, "f32"), (700, 1100, "f32"),
+                                       (701, 4001, "bf16"), (650, 5001, "f32"), (641, 2880, "bf16"), (655, 5120, "f32"),
+                                       (655, 5120, "bf16"), (645, 8192, "bf16"), (645, 8190, "f32"), (642, 8200, "f32")])
+def test_bulk_append_matches_oracle(oil, key_format, n, d, dtype):
+    """Bulk appends (from 640 rows, up to 8192 columns, rows aligned or not)
+    behind 13 rows, so their workgroups' rows straddle the call's ends; rows of
+    extreme norm, a zero row, negative zeros and quotients exactly halfway
+    between two stored values."""
+    g = torch.Generator().manual_seed(n + d)
+    raw = torch.randn((n + 13, d), generator=g)
+    raw[20] = 0
+    raw[21] *= 1e30
+    raw[22] *= 1e-30
+    raw[23, ::3] = -0.0
+    raw[24:28] = 0
+    for j, odd in enumerate((257, 259, 265, 273)):
+        # norm 512: odd / 512 lies halfway between bf16 values, 272 / 512 = 17 / 32 between E4M3 ones
+        rest = _four_squares(512 * 512 - odd * odd - 272 * 272)
+        raw[24 + j, :6] = torch.tensor([odd, -272, *rest], dtype=torch.float32)
+    raw = raw.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ids = torch.arange(n + 13, dtype=torch.int32)
+    pool = oil.Pool(d, n + 50, key_format=key_format)
+    pool.keys.zero_()
+    for s in (slice(0, 13), slice(13, n + 13)):
+        pool.append(raw[s].clone().cuda(), ids[s].cuda(), (ids[s] + 1).cuda(), (ids[s] + 2).cuda())
+    torch.cuda.synchronize()
+    if key_format == "bf16":
+        got, ref = _stored(pool, n + 13), oracle.normalize_rows(_raw_np(raw))
+        diff = np.abs(got.astype(np.int32) - ref.astype(np.int32))
+        past = untile_keys(_bits(pool.keys), n + 50, pool.stride, pool.capacity)
+    else:
+        got = untile_keys_fp8(pool.keys.cpu().numpy(), n + 13, d, pool.capacity)
+        ref, inv = oracle.quantize_rows_fp8(_raw_np(raw))
+        diff = np.abs(got.astype(np.int32) - ref.astype(np.int32))
+        assert np.array_equal(pool.scales.cpu().numpy()[:n + 13].astype(np.float64), inv)
+        past = untile_keys_fp8(pool.keys.cpu().numpy(), n + 50, pool.stride, pool.capacity)
+    # the norm's sum may round differently in its last bit: at most one step, hardly ever
+    assert diff.max() <= 1 and (diff > 0).mean() <= 1e-6
+    assert np.array_equal(got[20:28], ref[20:28])
+    assert np.all(past[:, d:] == 0) and np.all(past[n + 13:] == 0)
+    for t, off in ((pool.tokens, 0), (pool.traces, 1), (pool.prompts, 2)):
+        assert torch.equal(t[:n + 13].cpu(), ids + off)
 
 
 # ---------------------------------------------------------------- retrieval (Eq. 2)
