@@ -11,8 +11,8 @@
 //      counts of the trees before it (n_nodes - 1 - accept_len each) plus its
 //      rank among its tree's rejected nodes; its token and rollout go straight
 //      into the ring slot, its key's source row and slot into the workspace.
-//   2. recycle_keys_kernel: one 256-thread block per record normalises the
-//      source state as stored keys are normalised; block 0 advances the head.
+//   2. recycle_keys_kernel: one wave per record normalises the source state
+//      as stored keys are normalised; block 0 advances the head.
 //   Records a batch would itself overwrite (more than the capacity) are
 //   skipped, so no two blocks write one slot.
 // Lookup (four launches): normalise the queries; clear the match counts;
@@ -51,6 +51,7 @@ __global__ __launch_bounds__(256) void recycle_plan_kernel(
 {
     __shared__ int32_t par[OIL_NODES_MAX], tok[OIL_NODES_MAX], tgt[OIL_NODES_MAX];
     __shared__ uint32_t acc[OIL_NODES_MAX / 32];
+    __shared__ int32_t next_of[OIL_NODES_MAX];  // the first child carrying the node's prediction
     __shared__ int64_t red_base[4], red_total[4];
     __shared__ int32_t wsum[4];
     const int t = threadIdx.x, b = blockIdx.x, lane = t & 63, w = t >> 6;
@@ -87,6 +88,7 @@ __global__ __launch_bounds__(256) void recycle_plan_kernel(
     }
     if (t < OIL_NODES_MAX / 32)
         acc[t] = 0u;
+    next_of[t] = OIL_NODES_MAX;
     __syncthreads();
     base = red_base[0] + red_base[1] + red_base[2] + red_base[3];
     total = red_total[0] + red_total[1] + red_total[2] + red_total[3];
@@ -94,6 +96,13 @@ __global__ __launch_bounds__(256) void recycle_plan_kernel(
         const int a = accept_nodes[o + t];
         if (a >= 0 && a < max_nodes)
             atomicOr(&acc[a >> 5], 1u << (a & 31));
+    }
+    // every child at once (a walk that searches the children of each node in
+    // turn took 37 us for 32 trees of 65 slots, this 6)
+    if (t >= 1 && t < nn) {
+        const int p = par[t];
+        if (p >= 0 && p < nn && tok[t] == tgt[p])
+            atomicMin(&next_of[p], t);
     }
     __syncthreads();
     // rank of this node among the tree's rejected nodes (block exclusive scan)
@@ -121,14 +130,8 @@ __global__ __launch_bounds__(256) void recycle_plan_kernel(
     int cur = t, len = 0;
     out[len++] = tgt[cur];
     while (len < OIL_REC_DEPTH_MAX) {
-        int next = -1;
-        for (int c = 1; c < nn; c++) {
-            if (par[c] == cur && tok[c] == tgt[cur]) {
-                next = c;
-                break;
-            }
-        }
-        if (next < 0)
+        const int next = next_of[cur];
+        if (next >= nn)
             break;
         cur = next;
         out[len++] = tgt[cur];
@@ -144,7 +147,53 @@ __global__ __launch_bounds__(256) void recycle_plan_kernel(
     rec_slot[k] = (int32_t)slot;
 }
 
+// One wave per record: lane l takes the 8-column chunks l, l + 64, ... of the
+// row (NI of them hold it), which stays in registers between its norm and the
+// rounding.  VEC: whole 16-byte pieces of every row are aligned.  1,260
+// records of 4,096 bf16 columns (32 trees of 65 slots) 31 -> 14 us against a
+// 256-thread block per record that read each row twice and divided in double.
+template <bool F32, bool VEC, int NI>
 __global__ __launch_bounds__(256) void recycle_keys_kernel(
+    const void* __restrict__ states, int32_t d, int32_t ld, const int32_t* __restrict__ rec_src,
+    const int32_t* __restrict__ rec_slot, const int64_t* __restrict__ total_in, int64_t capacity,
+    uint16_t* __restrict__ keys, int64_t* __restrict__ head)
+{
+    const int64_t total = *total_in;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *head += total;  // no kernel of this call reads the head after the plan
+    const int lane = threadIdx.x & 63;
+    const int64_t first = total > capacity ? total - capacity : 0;
+    const int64_t k = first + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (k >= total)
+        return;
+    const int64_t at = (int64_t)rec_src[k] * d;
+    u32x4* dst = (u32x4*)(keys + (int64_t)rec_slot[k] * ld);
+    u32x4 x[NI][F32 ? 2 : 1];
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+        load_chunk<F32, VEC>(states, at, (i * 64 + lane) * 8, d, x[i]);
+    double ss = 0.0;
+#pragma unroll
+    for (int i = 0; i < NI; i++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const double v = chunk_value<F32>(x[i], e);
+            ss += v * v;
+        }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+        ss += __shfl_xor(ss, o, kWave);
+    const RowScale sc = row_scale(sqrt(ss));
+#pragma unroll
+    for (int i = 0; i < NI; i++) {
+        const int c = i * 64 + lane;
+        if (c < ld / 8)
+            dst[c] = unit_chunk_bf16<F32>(x[i], sc);
+    }
+}
+
+// The same for rows wider than 8,192 columns: one 256-thread block per record.
+__global__ __launch_bounds__(256) void recycle_wide_keys_kernel(
     const void* __restrict__ states, int dtype, int32_t d, int32_t ld, const int32_t* __restrict__ rec_src,
     const int32_t* __restrict__ rec_slot, const int64_t* __restrict__ total_in, int64_t capacity,
     uint16_t* __restrict__ keys, int64_t* __restrict__ head)
@@ -389,9 +438,24 @@ hipError_t launch_recycle_insert(int32_t B, int32_t max_nodes, const int32_t* no
     if (e != hipSuccess)
         return e;
     const int64_t most = (int64_t)B * (max_nodes - 1);
-    const int grid = (int)(most < 1 ? 1 : (most < 2048 ? most : 2048));
-    hipLaunchKernelGGL(recycle_keys_kernel, dim3(grid), dim3(256), 0, stream, states, dtype, d, ld, rec_src,
-                       rec_slot, total, capacity, keys, head);
+    if (ld > 8192) {
+        const int grid = (int)(most < 1 ? 1 : (most < 2048 ? most : 2048));
+        hipLaunchKernelGGL(recycle_wide_keys_kernel, dim3(grid), dim3(256), 0, stream, states, dtype, d, ld, rec_src,
+                           rec_slot, total, capacity, keys, head);
+        return hipGetLastError();
+    }
+    const bool f32 = dtype == 0, vec = ((int64_t)d * (f32 ? 4 : 2)) % 16 == 0, narrow = ld <= 4096;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(most < 1 ? 1 : (most + 3) / 4)), dim3(256), 0, stream, states, d,
+                           ld, rec_src, rec_slot, total, capacity, keys, head);
+    };
+    if (f32) {
+        if (vec) narrow ? go(recycle_keys_kernel<true, true, 8>) : go(recycle_keys_kernel<true, true, 16>);
+        else narrow ? go(recycle_keys_kernel<true, false, 8>) : go(recycle_keys_kernel<true, false, 16>);
+    } else {
+        if (vec) narrow ? go(recycle_keys_kernel<false, true, 8>) : go(recycle_keys_kernel<false, true, 16>);
+        else narrow ? go(recycle_keys_kernel<false, false, 8>) : go(recycle_keys_kernel<false, false, 16>);
+    }
     return hipGetLastError();
 }
 
