@@ -44,9 +44,6 @@ static __device__ __align__(256) unsigned char scratch[OIL_QUERY_SCRATCH_BYTES];
 namespace {
 
 constexpr size_t kAlign = 256;
-// Most scores the GEMV scan writes per call (2 MiB): past it the writes cost
-// the scan more than rescoring the chosen blocks.
-constexpr int64_t kFullScoresMax = 1 << 19;
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -56,10 +53,11 @@ int32_t hip_status(hipError_t e) { return e == hipSuccess ? OIL_OK : OIL_E_HIP; 
 
 struct QueryWorkspace {
     size_t q_off, sc_off, g_off, ca_off, cb_off, fs_off, total;
-    int64_t g_ld, fs_ld;  // fs_ld = 0: no full-score array (MFMA scans)
+    int64_t g_ld, fs_ld;  // fs_ld: positions per query of the full-score array (0: none)
 };
 
-QueryWorkspace carve(const oil_pool* p, int32_t B, int32_t k)
+// full: with room for the MFMA scan's full scores, which a call can do without.
+QueryWorkspace carve(const oil_pool* p, int32_t B, int32_t k, bool full = true)
 {
     QueryWorkspace w;
     const int tiles = oil::scan_query_tiles(B);
@@ -71,12 +69,13 @@ QueryWorkspace carve(const oil_pool* p, int32_t B, int32_t k)
     w.g_ld = oil::topk_block_ld(p->capacity);
     const size_t g_bytes = (size_t)B * (size_t)w.g_ld * sizeof(uint64_t);
     const size_t c_bytes = oil::topk_cand_bytes(B, k, p->capacity);
-    // the GEMV scan (bf16, B <= 4) writes every score instead of being
-    // rescored while B * n_valid <= kFullScoresMax (fs_ld per query, the
-    // positions a call may hold for that)
+    // a scan of at most fs_ld positions writes every score instead of being
+    // rescored: the GEMV scan (bf16, B <= 4) while B * n_valid <=
+    // kGemvScoresMax, the MFMA scan up to scan_full_rows positions
     const bool gemv = p->fmt != oil::kKeyFp8 && !oil::scan_uses_mfma(B, p->ld);
-    const int64_t fs_max = (kFullScoresMax / B) / 64 * 64;
-    w.fs_ld = gemv ? std::min((int64_t)round_up((size_t)p->capacity, 64), fs_max) : 0;
+    const int64_t fs_max = gemv ? (oil::kGemvScoresMax / B) / 64 * 64 : oil::scan_full_rows(B, k, (int64_t)p->ld * (p->fmt == oil::kKeyFp8 ? 1 : 2));
+    // (a pool past them never comes back: it needs no room)
+    w.fs_ld = gemv || (full && p->n_valid <= fs_max) ? std::min((int64_t)round_up((size_t)p->capacity, 64), fs_max) : 0;
     const size_t fs_bytes = (size_t)B * (size_t)w.fs_ld * sizeof(float);
     w.q_off = 0;
     w.sc_off = round_up(w.q_off + q_bytes, kAlign);
@@ -121,8 +120,9 @@ int32_t query_topk_enqueue(const oil_pool* pool, const void* queries, int32_t q_
     float* FS = (w.fs_ld && n_valid <= w.fs_ld) ? (float*)(ws + w.fs_off) : nullptr;
 
     const bool fp8 = pool->fmt == oil::kKeyFp8;
-    // the GEMV scan only where it writes every score; otherwise the MFMA scan
-    // (at 1M x 4096, B = 1 / 4: 1.208 / 1.207 ms against 1.232 / 1.250)
+    // the GEMV scan only where it writes every score (fs_ld bounds B * n_valid
+    // there); otherwise the MFMA scan (at 1M x 4096, B = 1 / 4: 1.208 / 1.207 ms
+    // against 1.232 / 1.250)
     const bool mfma = fp8 || oil::scan_uses_mfma(B, pool->ld) || !FS;
     const int tiles = oil::scan_query_tiles(B);
     float* qscale = fp8 ? (float*)(ws + w.q_off + (size_t)tiles * 32 * (size_t)pool->ld) : nullptr;
@@ -418,7 +418,9 @@ int32_t oil_pool_query_topk_noalloc(const oil_pool* pool, const void* queries, i
     const int32_t st = query_args_status(pool, queries, q_dtype, B, k, exclude_prompt, scores, idx);
     if (st != OIL_OK)
         return st;
-    const QueryWorkspace w = carve(pool, B, k);
+    QueryWorkspace w = carve(pool, B, k);
+    if (w.total > OIL_QUERY_SCRATCH_BYTES)
+        w = carve(pool, B, k, false);  // without the full scores: the chosen blocks are rescored
     if (w.total > OIL_QUERY_SCRATCH_BYTES)
         return OIL_E_SCRATCH;
     char* ws = nullptr;

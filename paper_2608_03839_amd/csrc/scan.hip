@@ -52,6 +52,7 @@
 // query's exclusion id get the "no position" bit pattern.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <numeric>
 #include <utility>
 
@@ -156,8 +157,31 @@ __device__ __forceinline__ void tile_rows_load(T (&out)[16], const T* __restrict
         }
 }
 
+// The 32 scores of one query column of a tile (v: the 16 rows a lane holds, as
+// in tile_rows_load) into the query's row of the full-score array, 16 bytes at
+// a time.  fs (the query's row at the tile's first position) is aligned to 128
+// bytes and holds whole row blocks; positions past the last stored one get
+// values nobody reads.
+__device__ __forceinline__ void store_tile_scores(float* __restrict__ fs, const floatx16& v, int h)
+{
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+        *(floatx4*)(fs + i * 8 + h * 4) = floatx4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
+}
+
 // ----------------------------------------------------------------- GEMV (B <= 4)
-template <int NB, int PF>
+// A persistent grid over the row blocks, each wave PF windows ahead, also
+// across the end of a row block.  Two workgroups per compute unit stream as
+// fast as a chip full of waves (65,536 x 4,096, one query: 80 us = 6.7 TB/s;
+// 320,000: 384 us) and leave registers and wave slots to kernels on other
+// streams: with one short-lived workgroup per four row blocks the lexical
+// source beside it got no slot before the scan's last generation.  On pools
+// of up to two row blocks per compute unit the four waves of a workgroup share a
+// row block (SPLIT: wave v takes windows v, v + 4, ...), where each wave's walk,
+// not memory, sets the time (4,096 wide, one query, us: 31 row blocks 14 -> 8,
+// 500 25 -> 22; past that splitting costs: 750 29 -> 32, 2,048 81 -> 103).
+constexpr int kGemvPf = 3, kGemvPerCu = 2;
+template <int NB, int PF, bool SPLIT>
 __global__ __launch_bounds__(256) void scan_gemv_kernel(
     const uint16_t* __restrict__ keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
     const uint16_t* __restrict__ q, const int32_t* __restrict__ prompt,
@@ -166,69 +190,97 @@ __global__ __launch_bounds__(256) void scan_gemv_kernel(
 {
     constexpr int NS = PF + 1;
     extern __shared__ __align__(16) uint16_t q_lds[];  // NB x ld, row-major
+    __shared__ float part[SPLIT ? 4 : 1][NB][kRowBlock];  // SPLIT: partial scores of the four waves
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = lane >> 5, r = lane & 31;
+    const int64_t n_rb = (n_valid + kRowBlock - 1) / kRowBlock;
+    const int nwin = ld / kWindow;
+    const int nq = SPLIT ? (nwin + 3) / 4 : nwin;  // windows of a wave per row block
+    const int64_t ws8 = ws / 8, rs8 = rs / 8;
+    const bf16x8* kv = (const bf16x8*)keys + lane;
+    const int64_t stride = SPLIT ? gridDim.x : (int64_t)gridDim.x * 4;
+    int64_t rb = SPLIT ? blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
+    const bool idle = rb >= n_rb;  // a wave past the pool only stages the queries
+    // step i of a row block is window i (SPLIT: 4 i + wave); steps run to a whole
+    // number of rings, so that every row block starts in stage 0
+    const int nloop = (nq + NS - 1) / NS * NS;
+    bf16x8 a[NS][4];
+    auto request = [&](bf16x8 (&dst)[4], int64_t at_rb, int i) {
+        const int wl = SPLIT ? 4 * i + wave : i;
+        const int64_t at = at_rb * rs8 + (wl < nwin ? wl : nwin - 1) * ws8;
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+            dst[s] = __builtin_nontemporal_load(kv + at + s * 64);
+    };
+#pragma unroll
+    for (int p = 0; p < PF; p++)
+        request(a[p], idle ? n_rb - 1 : rb, p);
     for (int64_t j = threadIdx.x * 8; j < (int64_t)NB * ld; j += 256 * 8)
         *(bf16x8*)(q_lds + j) = *(const bf16x8*)(q + j);
     __syncthreads();
-
-    const int lane = threadIdx.x & 63;
-    const int h = lane >> 5, r = lane & 31;
-    const int64_t rb = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (rb * kRowBlock >= n_valid)
+    if (idle)
         return;
-    const int nwin = ld / kWindow;
-    const bf16x8* tile = (const bf16x8*)(keys + rb * rs) + lane;
-    const int64_t ws8 = ws / 8;
-
     float acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++)
         acc[b] = 0.f;
-    bf16x8 a[NS][4];
+    for (; rb < n_rb; rb += stride) {
+        const int64_t next = rb + stride < n_rb ? rb + stride : rb;  // after the last row block: loads nobody uses
+        for (int i0 = 0; i0 < nloop; i0 += NS) {
 #pragma unroll
-    for (int p = 0; p < PF; p++) {
-        const int w = p < nwin ? p : nwin - 1;
+            for (int u = 0; u < NS; u++) {
+                const int il = i0 + u + PF;
+                request(a[(u + PF) % NS], il < nloop ? rb : next, il < nloop ? il : il - nloop);
+                const int w = SPLIT ? 4 * (i0 + u) + wave : i0 + u;
+                if (w < nwin) {
+                    const int col = w * kWindow + 32 * h;
 #pragma unroll
-        for (int s = 0; s < 4; s++)
-            a[p][s] = __builtin_nontemporal_load(tile + w * ws8 + s * 64);
-    }
-    const int nloop = (nwin + NS - 1) / NS * NS;
-    for (int w0 = 0; w0 < nloop; w0 += NS) {
+                    for (int s = 0; s < 4; s++)
 #pragma unroll
-        for (int u = 0; u < NS; u++) {
-            const int wl = w0 + u + PF < nwin ? w0 + u + PF : nwin - 1;
-#pragma unroll
-            for (int s = 0; s < 4; s++)
-                a[(u + PF) % NS][s] = __builtin_nontemporal_load(tile + wl * ws8 + s * 64);
-            if (w0 + u < nwin) {
-                const int col = (w0 + u) * kWindow + 32 * h;
-#pragma unroll
-                for (int s = 0; s < 4; s++)
-#pragma unroll
-                    for (int b = 0; b < NB; b++)
-                        acc[b] = dot8_bf16(a[u][s], *(const bf16x8*)(q_lds + b * ld + col + 8 * s),
-                                           acc[b]);
+                        for (int b = 0; b < NB; b++)
+                            acc[b] = dot8_bf16(a[u][s], *(const bf16x8*)(q_lds + b * ld + col + 8 * s),
+                                               acc[b]);
+                }
             }
         }
-    }
-    // Lanes r and r + 32 now both hold row r's full score: lane r stores it,
-    // and each query keeps the best (score, position) key of this row block.
-    const int64_t row = rb * kRowBlock + r;
+        // the row block's scores: lanes r and r + 32 of a wave hold row r's
+        // two column halves
+        auto finish = [&](int b, float full) {
+            const int64_t row = rb * kRowBlock + r;
+            const int32_t ex = exclude ? exclude[b] : -1;
+            const bool have = row < n_valid;
+            const float v = have ? masked_score(full, row, ex, prompt) : 0.f;
+            if (FS && have && h == 0)
+                FS[b * fs_ld + row] = v;
+            uint64_t best = have ? rank_key(v, (uint32_t)row) : 0ull;
 #pragma unroll
-    for (int b = 0; b < NB; b++) {
-        const float full = acc[b] + __shfl_xor(acc[b], 32, kWave);
-        const int32_t ex = exclude ? exclude[b] : -1;
-        const bool have = row < n_valid;
-        const float v = have ? masked_score(full, row, ex, prompt) : 0.f;
-        if (FS && have && h == 0)
-            FS[b * fs_ld + row] = v;
-        uint64_t best = have ? rank_key(v, (uint32_t)row) : 0ull;
+            for (int o = 16; o >= 1; o >>= 1) {
+                const uint64_t other = __shfl_xor(best, o, kWave);
+                best = other > best ? other : best;
+            }
+            if (lane == 0)
+                G[b * g_ld + rb] = best;
+        };
+        if constexpr (SPLIT) {
+            // the waves' parts meet in LDS and wave b finishes query b (the
+            // grid has a workgroup per row block: one round)
 #pragma unroll
-        for (int o = 16; o >= 1; o >>= 1) {
-            const uint64_t other = __shfl_xor(best, o, kWave);
-            best = other > best ? other : best;
+            for (int b = 0; b < NB; b++) {
+                const float full = acc[b] + __shfl_xor(acc[b], 32, kWave);
+                if (h == 0)
+                    part[wave][b][r] = full;
+                acc[b] = 0.f;
+            }
+            __syncthreads();
+            if (wave < NB)
+                finish(wave, (part[0][wave][r] + part[1][wave][r]) + (part[2][wave][r] + part[3][wave][r]));
+        } else {
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+                finish(b, acc[b] + __shfl_xor(acc[b], 32, kWave));
+                acc[b] = 0.f;
+            }
         }
-        if (lane == 0)
-            G[b * g_ld + rb] = best;
     }
 }
 
@@ -275,12 +327,13 @@ __device__ __forceinline__ void load_window(bf16x8 (&a)[MT][4], bf16x8 (&b)[NT][
             b[nt][s] = qf[(((int64_t)w * NT + nt) * 4 + s) * 64];
 }
 
-template <int MT, int NT, int PF, int FMT>
+template <int MT, int NT, int PF, int FMT, bool FULL>
 __global__ __launch_bounds__(256) void scan_mfma_kernel(
     const uint16_t* __restrict__ keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
     const bf16x8* __restrict__ qfrag, int32_t B, const int32_t* __restrict__ prompt,
     const int32_t* __restrict__ exclude, uint64_t* __restrict__ G, int64_t g_ld,
-    const float* __restrict__ kscale, const float* __restrict__ qscale, int64_t rb_base)
+    const float* __restrict__ kscale, const float* __restrict__ qscale, int64_t rb_base, float* __restrict__ FS,
+    int64_t fs_ld)
 {
     constexpr int NS = PF + 1;
     const int lane = threadIdx.x & 63;
@@ -382,10 +435,14 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(
                         v = v * (ks[e] * qs[nt]);  // powers of two: exact
                     if (ex[nt] >= 0 && pr[e] == ex[nt])
                         v = __uint_as_float(kNoScoreBits);
+                    if constexpr (FULL)
+                        acc[mt][nt][e] = v;
                     const uint64_t key = rank_key(v, (uint32_t)row);
                     best = key > best ? key : best;
                 }
             }
+            if (FULL && FS && nt * 32 + r < B && rb < n_rb)
+                store_tile_scores(FS + (nt * 32 + r) * fs_ld + rb * kRowBlock, acc[mt][nt], h);
             const uint64_t other = __shfl_xor(best, 32, kWave);
             best = other > best ? other : best;
             if (h == 0)
@@ -620,13 +677,13 @@ __device__ __forceinline__ void unrolled(F&& f)
     unrolled_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-template <int MT, int NTW, int R, int NB, int WAVES, int WPE, int FMT, int RS, int SKIP>
+template <int MT, int NTW, int R, int NB, int WAVES, int WPE, int FMT, int RS, int SKIP, bool FULL>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WPE))) void
 scan_mfma_wide_kernel(
     const uint16_t* __restrict__ keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
     const bf16x8* __restrict__ qfrag, int32_t B, const int32_t* __restrict__ prompt,
     const int32_t* __restrict__ exclude, uint64_t* __restrict__ G, int64_t g_ld,
-    const float* __restrict__ kscale, const float* __restrict__ qscale)
+    const float* __restrict__ kscale, const float* __restrict__ qscale, float* __restrict__ FS, int64_t fs_ld)
 {
     constexpr int NG = FMT == kKeyBf16 ? 4 : 2;  // MFMA groups per window
     constexpr int CG = 4 / NG;                   // 1 KiB operand chunks per group
@@ -854,10 +911,14 @@ scan_mfma_wide_kernel(
                         v = v * (ks[e] * qs[nt]);  // powers of two: exact, as the narrow scan scales it
                     if (ex[nt] >= 0 && pr[e] == ex[nt])
                         v = __uint_as_float(kNoScoreBits);
+                    if constexpr (FULL)
+                        t[e] = v;
                     const uint64_t key = rank_key(v, (uint32_t)row);
                     best = key > best ? key : best;
                 }
             }
+            if (FULL && FS && qb < B && rb < n_rb)
+                store_tile_scores(FS + qb * fs_ld + rb * kRowBlock, t, h);
             const uint64_t other = __shfl_xor(best, 32, kWave);
             best = other > best ? other : best;
             // streamed past the caches up to four query tiles (B = 128: 1.498
@@ -899,7 +960,8 @@ __global__ __launch_bounds__(64 * (NT + 4)) void scan_tail_kernel(
     const uint16_t* __restrict__ keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
     const bf16x8* __restrict__ qfrag, int32_t B, const int32_t* __restrict__ prompt,
     const int32_t* __restrict__ exclude, uint64_t* __restrict__ G, int64_t g_ld,
-    const float* __restrict__ kscale, const float* __restrict__ qscale, int64_t rb_base)
+    const float* __restrict__ kscale, const float* __restrict__ qscale, int64_t rb_base, float* __restrict__ FS,
+    int64_t fs_ld)
 {
     constexpr int TC = OIL_TAIL_TC, TS = OIL_TAIL_TS;
     constexpr int TP = TC - 1;  // fragment prefetch distance (windows); set of window w: w % TC
@@ -1035,10 +1097,13 @@ __global__ __launch_bounds__(64 * (NT + 4)) void scan_tail_kernel(
                 v = v * (ks[e] * qs);  // powers of two: exact
             if (ex >= 0 && pr[e] == ex)
                 v = __uint_as_float(kNoScoreBits);
+            acc[e] = v;
             const uint64_t key = rank_key(v, (uint32_t)row);
             best = key > best ? key : best;
         }
     }
+    if (FS && qlive)
+        store_tile_scores(FS + qb * fs_ld + rb * kRowBlock, acc, h);
     const uint64_t other = __shfl_xor(best, 32, kWave);
     best = other > best ? other : best;
     if (qlive && h == 0)
@@ -1170,13 +1235,17 @@ static void dispatch(const ScanLaunch& sl, bool first, bool last, K kernel, dim3
 }
 
 template <int NB>
-static void launch_gemv(dim3 g, size_t lds, const ScanLaunch& sl, const uint16_t* keys, int32_t ld,
+static void launch_gemv(bool split, dim3 g, size_t lds, const ScanLaunch& sl, const uint16_t* keys, int32_t ld,
                         int64_t rs, int64_t ws, int64_t n_valid, const uint16_t* q,
                         const int32_t* prompt, const int32_t* exclude, uint64_t* G, int64_t g_ld, float* FS,
                         int64_t fs_ld)
 {
-    dispatch(sl, true, true, scan_gemv_kernel<NB, 3>, g, lds, keys, ld, rs, ws, n_valid, q, prompt, exclude, G,
-             g_ld, FS, fs_ld);
+    if (split)
+        dispatch(sl, true, true, scan_gemv_kernel<NB, kGemvPf, true>, g, lds, keys, ld, rs, ws, n_valid, q, prompt,
+                 exclude, G, g_ld, FS, fs_ld);
+    else
+        dispatch(sl, true, true, scan_gemv_kernel<NB, kGemvPf, false>, g, lds, keys, ld, rs, ws, n_valid, q, prompt,
+                 exclude, G, g_ld, FS, fs_ld);
 }
 
 static bool nwin_even(int32_t ld, int fmt) { return (ld / (fmt == kKeyBf16 ? kWindow : kWindowFp8)) % 2 == 0; }
@@ -1207,8 +1276,33 @@ static int device_cus()
 template <int MT, int NT, int PF, int TPF, int FMT>
 static void launch_narrow(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid, int64_t n_rb,
                           const bf16x8* qf, int32_t B, const int32_t* prompt, const int32_t* exclude,
-                          uint64_t* G, int64_t g_ld, const float* kscale, const float* qscale, const ScanLaunch& sl)
+                          uint64_t* G, int64_t g_ld, const float* kscale, const float* qscale, const ScanLaunch& sl,
+                          float* FS, int64_t fs_ld)
 {
+    // Pools too small to give every SIMD a wave of MT row blocks: one row
+    // block per workgroup of the remainder kernel up to two per compute unit,
+    // then one and two row blocks per wave up to one wave per SIMD.  4,096
+    // These write every score where the caller has room (FS).  4,096
+    // wide, 8 queries, us (bf16 keys, remainder kernel / 1 / 2 / 4 row blocks
+    // per wave): 250 row blocks 15 / 32 / 50 / 84; 500 29 / 35 / 54 / 89;
+    // 1,000 59 / 42 / 60 / 95; 2,000 132 / 82 / 77 / 105; 3,125 - / 141 / 137 /
+    // 123.  64 queries and fp8 keys change places at the same sizes.
+    const int64_t cus = device_cus();
+    if (n_rb <= cus || (n_rb <= 2 * cus && ld * (FMT == kKeyBf16 ? 2 : 1) >= 1024)) {  // (short rows: 8.8 against 10)
+        dispatch_n(sl, true, true, scan_tail_kernel<NT, FMT>, dim3((unsigned)n_rb), dim3(64 * (NT + 4)), 0, keys, ld,
+                   rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, (int64_t)0, FS, fs_ld);
+        return;
+    }
+    if (n_rb <= 4 * cus) {
+        dispatch(sl, true, true, scan_mfma_kernel<1, NT, TPF, FMT, true>, dim3((unsigned)((n_rb + 3) / 4)), 0, keys, ld, rs,
+                 ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, (int64_t)0, FS, fs_ld);
+        return;
+    }
+    if (FS || (MT > 2 && n_rb <= 8 * cus)) {
+        dispatch(sl, true, true, scan_mfma_kernel<2, NT, 1, FMT, true>, dim3((unsigned)((n_rb + 7) / 8)), 0, keys, ld, rs,
+                 ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, (int64_t)0, FS, fs_ld);
+        return;
+    }
     constexpr int kWavesPerSimd = NT == 1 ? 2 : 1;  // what the kernels' register use allows
     const int64_t gen = (int64_t)device_cus() * 4 * kWavesPerSimd * MT;
     // Measured on 1M x 4096 (B = 32, four generations): a remainder of 1-15
@@ -1261,19 +1355,19 @@ static void launch_narrow(const uint16_t* keys, int32_t ld, int64_t rs, int64_t 
             if (rem > 0)
                 dispatch_n(sl, false, true, scan_tail_kernel<NT, FMT>, dim3((unsigned)rem), dim3(64 * (NT + 4)), 0,
                            keys, ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale,
-                           n_groups * grp);
+                           n_groups * grp, (float*)nullptr, (int64_t)0);
             return;
         }
     }
-    dispatch(sl, true, n_tail == 0, scan_mfma_kernel<MT, NT, PF, FMT>,
+    dispatch(sl, true, n_tail == 0, scan_mfma_kernel<MT, NT, PF, FMT, false>,
              dim3((unsigned)((n_main + 4 * MT - 1) / (4 * MT))), 0, keys, ld, rs, ws, n_valid, qf, B, prompt,
-             exclude, G, g_ld, kscale, qscale, (int64_t)0);
+             exclude, G, g_ld, kscale, qscale, (int64_t)0, (float*)nullptr, (int64_t)0);
     if (lds_tail)
         dispatch_n(sl, false, true, scan_tail_kernel<NT, FMT>, dim3((unsigned)n_tail), dim3(64 * (NT + 4)), 0,
-                   keys, ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, n_main);
+                   keys, ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, n_main, (float*)nullptr, (int64_t)0);
     else if (n_tail > 0)
-        dispatch(sl, false, true, scan_mfma_kernel<1, NT, TPF, FMT>, dim3((unsigned)((n_tail + 3) / 4)), 0, keys,
-                 ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, n_main);
+        dispatch(sl, false, true, scan_mfma_kernel<1, NT, TPF, FMT, true>, dim3((unsigned)((n_tail + 3) / 4)), 0, keys,
+                 ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, n_main, (float*)nullptr, (int64_t)0);
 }
 
 // The wide scan (64 < B <= 512), either key format: one configuration per
@@ -1281,22 +1375,22 @@ static void launch_narrow(const uint16_t* keys, int32_t ld, int64_t rs, int64_t 
 // RS): row blocks per workgroup, key windows in the LDS ring, fragment
 // register sets, waves per workgroup, the waves per SIMD the registers must
 // allow, and the waves that split a tile's row blocks.
-template <int MT, int R, int NB, int WAVES, int WPE, int RS, int TILES, int FMT>
+template <int MT, int R, int NB, int WAVES, int WPE, int RS, int TILES, int FMT, bool FULL = false>
 static void launch_wide_cfg(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
                             int64_t n_rb, const bf16x8* qf, int32_t B, const int32_t* prompt,
                             const int32_t* exclude, uint64_t* G, int64_t g_ld, const float* kscale,
-                            const float* qscale, const ScanLaunch& sl)
+                            const float* qscale, const ScanLaunch& sl, float* FS, int64_t fs_ld)
 {
     constexpr int NTW = TILES * RS / WAVES;
     static_assert(NTW * WAVES == TILES * RS, "query tiles per wave");
     const dim3 grid((unsigned)((n_rb + MT - 1) / MT)), block(64 * WAVES);
     // a batch that fills the class's tiles runs without the skip branches
-    if (scan_query_tiles(B) == TILES)
-        dispatch_n(sl, true, true, scan_mfma_wide_kernel<MT, NTW, R, NB, WAVES, WPE, FMT, RS, 0>, grid, block, 0, keys,
-                   ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale);
+    if (!FULL && scan_query_tiles(B) == TILES)
+        dispatch_n(sl, true, true, scan_mfma_wide_kernel<MT, NTW, R, NB, WAVES, WPE, FMT, RS, FULL, FULL>, grid, block, 0,
+                   keys, ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, FS, fs_ld);
     else
-        dispatch_n(sl, true, true, scan_mfma_wide_kernel<MT, NTW, R, NB, WAVES, WPE, FMT, RS, 1>, grid, block, 0, keys,
-                   ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale);
+        dispatch_n(sl, true, true, scan_mfma_wide_kernel<MT, NTW, R, NB, WAVES, WPE, FMT, RS, 1, FULL>, grid, block, 0,
+                   keys, ld, rs, ws, n_valid, qf, B, prompt, exclude, G, g_ld, kscale, qscale, FS, fs_ld);
 }
 
 // Configurations (MT, R, NB, WAVES, WPE, RS) per class, measured on
@@ -1334,20 +1428,73 @@ static void launch_wide_cfg(const uint16_t* keys, int32_t ld, int64_t rs, int64_
 template <int FMT>
 static void launch_wide(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid, int64_t n_rb,
                         const bf16x8* qf, int32_t B, const int32_t* prompt, const int32_t* exclude, uint64_t* G,
-                        int64_t g_ld, const float* kscale, const float* qscale, const ScanLaunch& sl)
+                        int64_t g_ld, const float* kscale, const float* qscale, const ScanLaunch& sl, float* FS,
+                        int64_t fs_ld)
 {
     const int n_qt = scan_query_tiles(B);
-#define OIL_WIDE_ARGS keys, ld, rs, ws, n_valid, n_rb, qf, B, prompt, exclude, G, g_ld, kscale, qscale, sl
-    if constexpr (FMT == kKeyBf16) {
-        if (n_qt <= 4) launch_wide_cfg<OIL_WIDE_C1, 4, FMT>(OIL_WIDE_ARGS);
-        else if (n_qt <= 8) launch_wide_cfg<OIL_WIDE_C2, 8, FMT>(OIL_WIDE_ARGS);
-        else launch_wide_cfg<OIL_WIDE_C4, 16, FMT>(OIL_WIDE_ARGS);
+    constexpr bool bf = FMT == kKeyBf16;
+    // Pools of fewer than one workgroup of the full configurations per compute
+    // unit: 1, 2 or 4 row blocks per workgroup, the most that still give every
+    // compute unit one.  With FS every kernel writes every score.
+    // 4,096 wide, us (bf16 keys, 1 / 2 / 4 / the full configuration's row
+    // blocks): 125 row blocks, 128 queries 26 / 32 / 41 / 60, 512 queries 56 / 62
+    // / 79; 500 row blocks 46 / 37 / 45 / 65 and 106 / 70 / 85; 1,000 row blocks
+    // 90 / 70 / 52 / 73 and 200 / 135 / 113; fp8 keys alike.
+    const int64_t cus = device_cus();
+    const int mt = n_rb <= cus ? 1 : n_rb <= 2 * cus ? 2 : n_rb <= 4 * cus ? 4 : 0;
+#define OIL_WIDE_ARGS keys, ld, rs, ws, n_valid, n_rb, qf, B, prompt, exclude, G, g_ld, kscale, qscale, sl, FS, fs_ld
+    auto cls = [&](auto tiles_t, auto base) {
+        constexpr int T = decltype(tiles_t)::value;
+        constexpr int W2 = 2;                   // waves per SIMD
+        constexpr int RS = T == 4 ? 2 : 1;      // waves that share a tile's row blocks
+        constexpr int W4 = bf || T < 16 ? 8 : 4;  // waves of the 4-row-block kernel (fp8, 16 tiles: 4 of 4 tiles)
+        if (mt == 1)
+            launch_wide_cfg<1, 4, 2, 4, T == 16 ? 1 : W2, 1, T, FMT, true>(OIL_WIDE_ARGS);
+        else if (mt == 2)
+            launch_wide_cfg<2, 4, 2, 8, W2, RS, T, FMT, true>(OIL_WIDE_ARGS);
+        else if (mt == 4)
+            launch_wide_cfg<4, 4, 2, W4, W4 / 4, RS, T, FMT, true>(OIL_WIDE_ARGS);
+        else
+            base();
+    };
+#define OIL_WIDE_BASE(CFG, T)                                                                 \
+    cls(std::integral_constant<int, T>{}, [&] {                                               \
+        FS ? launch_wide_cfg<CFG, T, FMT, true>(OIL_WIDE_ARGS) : launch_wide_cfg<CFG, T, FMT>(OIL_WIDE_ARGS); \
+    })
+    if constexpr (bf) {
+        if (n_qt <= 4) OIL_WIDE_BASE(OIL_WIDE_C1, 4);
+        else if (n_qt <= 8) OIL_WIDE_BASE(OIL_WIDE_C2, 8);
+        else OIL_WIDE_BASE(OIL_WIDE_C4, 16);
     } else {
-        if (n_qt <= 4) launch_wide_cfg<OIL_WIDE_F1, 4, FMT>(OIL_WIDE_ARGS);
-        else if (n_qt <= 8) launch_wide_cfg<OIL_WIDE_F2, 8, FMT>(OIL_WIDE_ARGS);
-        else launch_wide_cfg<OIL_WIDE_F4, 16, FMT>(OIL_WIDE_ARGS);
+        if (n_qt <= 4) OIL_WIDE_BASE(OIL_WIDE_F1, 4);
+        else if (n_qt <= 8) OIL_WIDE_BASE(OIL_WIDE_F2, 8);
+        else OIL_WIDE_BASE(OIL_WIDE_F4, 16);
     }
+#undef OIL_WIDE_BASE
 #undef OIL_WIDE_ARGS
+}
+
+// Positions up to which the MFMA scan of a batch writes every score, so that
+// the final selection reads the chosen blocks' scores instead of rescoring
+// them.  The scores are B n_valid 4 bytes, the rescored blocks B k 32
+// row_bytes; per byte the stores cost the HBM-bound scans more.
+//  * Up to 64 queries: the pools of the kernels above that take few row blocks
+//    per wave (16 MiB of scores at most).  There the rescore (B k waves, each a
+//    chain of loads as long as a row) costs as much as the scan, the stores next
+//    to nothing: 8,000 x 4,096, 16 queries, k = 16: 24 us against under 1.  On
+//    larger pools the stores cost the scan more (128 MB at 1M positions: 200 us).
+//  * Above: where the stores cost less than the rescore.  4,096 wide, k = 16,
+//    whole call, us, rescored / with full scores: 128,000 positions, 100 / 200 /
+//    512 queries 262 / 391 / 804 against 225 / 289 / 551; 400,001 positions
+//    663 / 975 / 1,804 against 692 / 894 / 1,692; 800,000 positions 1,216 /
+//    1,777 / 3,254 against 1,449 / 1,749 / 3,402; fp8 keys, 400,001 positions
+//    390 / 600 / 1,087 against 416 / 592 / 1,056.  At most 1 GiB.
+int64_t scan_full_rows(int32_t B, int32_t k, int64_t row_bytes)
+{
+    if (B <= 64)
+        return 2048 * kRowBlock;
+    const int64_t even = (int64_t)k * kRowBlock * row_bytes / (B <= 128 ? 14 : 5);
+    return std::max<int64_t>(1024 * kRowBlock, std::min<int64_t>(even, (1 << 28) / B) / 64 * 64);
 }
 
 hipError_t launch_scan(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
@@ -1364,40 +1511,43 @@ hipError_t launch_scan(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws,
         const bf16x8* qf = (const bf16x8*)qbuf;
         if (B > 64)
             launch_wide<kKeyFp8>(keys, ld, rs, ws, n_valid, n_rb, qf, B, prompt, exclude, G, g_ld, kscale, qscale,
-                                 sl);
+                                 sl, FS, fs_ld);
         else if (scan_query_tiles(B) == 1)
             launch_narrow<MT, 1, PF, OIL_TAIL_PF1, kKeyFp8>(keys, ld, rs, ws, n_valid, n_rb, qf, B, prompt, exclude,
-                                                            G, g_ld, kscale, qscale, sl);
+                                                            G, g_ld, kscale, qscale, sl, FS, fs_ld);
         else
             launch_narrow<MT2, 2, PF, OIL_TAIL_PF2, kKeyFp8>(keys, ld, rs, ws, n_valid, n_rb, qf, B, prompt, exclude,
-                                                             G, g_ld, kscale, qscale, sl);
+                                                             G, g_ld, kscale, qscale, sl, FS, fs_ld);
         return hipGetLastError();
     }
-    if (!scan_uses_mfma(B, ld) && FS) {  // the GEMV scan only where it writes every score
-        const dim3 g((unsigned)((n_rb + 3) / 4));
+    if (!scan_uses_mfma(B, ld) && FS && (int64_t)B * n_valid <= kGemvScoresMax) {  // the GEMV scan only where it writes every score
+        const bool split = n_rb <= 2 * (int64_t)device_cus();
+        const int64_t most = (int64_t)device_cus() * 4 * kGemvPerCu, rounds = (n_rb + most - 1) / most;
+        // every wave as many row blocks, or one less
+        const dim3 g((unsigned)(split ? n_rb : ((n_rb + rounds - 1) / rounds + 3) / 4));
         const size_t lds = (size_t)B * ld * sizeof(uint16_t);
         const uint16_t* q = (const uint16_t*)qbuf;
         switch (B) {
-        case 1: launch_gemv<1>(g, lds, sl, keys, ld, rs, ws, n_valid, q, prompt, exclude, G, g_ld, FS, fs_ld); break;
-        case 2: launch_gemv<2>(g, lds, sl, keys, ld, rs, ws, n_valid, q, prompt, exclude, G, g_ld, FS, fs_ld); break;
-        case 3: launch_gemv<3>(g, lds, sl, keys, ld, rs, ws, n_valid, q, prompt, exclude, G, g_ld, FS, fs_ld); break;
-        default: launch_gemv<4>(g, lds, sl, keys, ld, rs, ws, n_valid, q, prompt, exclude, G, g_ld, FS, fs_ld); break;
+        case 1: launch_gemv<1>(split, g, lds, sl, keys, ld, rs, ws, n_valid, q, prompt, exclude, G, g_ld, FS, fs_ld); break;
+        case 2: launch_gemv<2>(split, g, lds, sl, keys, ld, rs, ws, n_valid, q, prompt, exclude, G, g_ld, FS, fs_ld); break;
+        case 3: launch_gemv<3>(split, g, lds, sl, keys, ld, rs, ws, n_valid, q, prompt, exclude, G, g_ld, FS, fs_ld); break;
+        default: launch_gemv<4>(split, g, lds, sl, keys, ld, rs, ws, n_valid, q, prompt, exclude, G, g_ld, FS, fs_ld); break;
         }
         return hipGetLastError();
     }
     const bf16x8* qf = (const bf16x8*)qbuf;
     if (B > 64) {
         launch_wide<kKeyBf16>(keys, ld, rs, ws, n_valid, n_rb, qf, B, prompt, exclude, G, g_ld, nullptr, nullptr,
-                              sl);
+                              sl, FS, fs_ld);
         return hipGetLastError();
     }
     constexpr int MT = OIL_BF16_MT, MT2 = OIL_BF16_MT2, PF = OIL_BF16_PF;
     if (scan_query_tiles(B) == 1)
         launch_narrow<MT, 1, PF, OIL_TAIL_PF1, kKeyBf16>(keys, ld, rs, ws, n_valid, n_rb, qf, B, prompt, exclude, G,
-                                                         g_ld, nullptr, nullptr, sl);
+                                                         g_ld, nullptr, nullptr, sl, FS, fs_ld);
     else
         launch_narrow<MT2, 2, PF, OIL_TAIL_PF2, kKeyBf16>(keys, ld, rs, ws, n_valid, n_rb, qf, B, prompt, exclude, G,
-                                                          g_ld, nullptr, nullptr, sl);
+                                                          g_ld, nullptr, nullptr, sl, FS, fs_ld);
     return hipGetLastError();
 }
 

@@ -869,3 +869,50 @@ def test_scores_independent_of_batch_companions(oil, key_format):
     for s_, i_ in results[1:]:
         assert torch.equal(i_, i0)
         assert torch.equal(s_.view(torch.int32), s0.view(torch.int32))
+
+
+def _small_pool_rows(B):
+    """Pool sizes around the scan's changes of kernel on a 256-unit chip: one
+    and two row blocks per unit (remainder kernel, one or two row blocks per
+    wide workgroup), one and two per wave, the last pool with full scores."""
+    if B <= 64:
+        return [31, 256 * 32, 256 * 32 + 1, 512 * 32, 512 * 32 + 7, 1024 * 32 + 1, 2048 * 32, 2048 * 32 + 1]
+    return [31, 256 * 32, 256 * 32 + 5, 512 * 32, 512 * 32 + 1, 1024 * 32, 1024 * 32 + 1, 1300 * 32 + 9]
+
+
+@pytest.mark.parametrize("key_format", ["bf16", "fp8"])
+@pytest.mark.parametrize("B", [1, 4, 7, 33, 64, 65, 128, 160, 300, 512])
+def test_small_pool_kernels_agree(oil, key_format, B):
+    """One capacity, pools cut at every size where the scan changes kernel: the
+    top-k of each equals the best of its prefix by exact scores (the same
+    selection rules as everywhere), with the queries' own prompts excluded, and
+    is bit-identical to the allocation-free call, whose scratch may hold no
+    full scores, so that the chosen blocks are rescored there."""
+    d, k = 256, 24
+    sizes = _small_pool_rows(B)
+    n = sizes[-1]
+    wp = workloads.Pool(workloads.PoolSpec(n=n, d=d, vocab=100, seed=61 + B, n_clusters=64, key_dtype="f32"), device="cuda")
+    raw = wp.raw_rows(0, n)
+    pool = oil.Pool(d, n + 77, key_format=key_format)
+    prompts = (torch.arange(n, dtype=torch.int32) // 48)
+    q, src = workloads.queries(wp, workloads.QuerySpec(B=B, p_random=0.25, seed=62), n_valid=31)
+    ex = torch.where(src >= 0, prompts[src.clamp(min=0)], torch.full_like(src, -1)).to(torch.int32).cuda()
+    at = 0
+    for m in sizes:
+        pool.append(raw[at:m], wp.tokens[at:m].cuda(), wp.traces[at:m].cuda(), prompts[at:m].cuda())
+        at = m
+        s, i = pool.query_topk(q.cuda(), k, exclude_prompt=ex)
+        s2, i2 = torch.empty_like(s), torch.empty_like(i)
+        oil.pool_query_topk_noalloc(pool.handle, q.cuda(), k, s2, i2, exclude_prompt=ex)
+        torch.cuda.synchronize()
+        assert torch.equal(i, i2) and torch.equal(s.view(torch.int32), s2.view(torch.int32))
+        if key_format == "bf16":
+            o = oracle_rows(_stored(pool, m), q.cpu().numpy(), prompts[:m].numpy(), ex.cpu().numpy())
+        else:
+            kc = untile_keys_fp8(pool.keys.cpu().numpy(), m, d, pool.capacity)
+            qc, qi = oracle.quantize_rows_fp8(q.cpu().numpy())
+            o = oracle.scores_fp8(kc, pool.scales[:m].cpu().numpy().astype(np.float64), qc, qi)
+            for b, e in enumerate(ex.cpu().numpy()):
+                if e >= 0:
+                    o[b, prompts[:m].numpy() == e] = -np.inf
+        check_topk(s.cpu().numpy(), i.cpu().numpy(), o, k, eps=fp32_bound(d, key_format))
