@@ -15,7 +15,7 @@
 //      as stored keys are normalised; block 0 advances the head.
 //   Records a batch would itself overwrite (more than the capacity) are
 //   skipped, so no two blocks write one slot.
-// Lookup (four launches): normalise the queries; clear the match counts;
+// Lookup (three launches): normalise the queries and clear the match counts;
 // recycle_match_kernel lists, per request, the records carrying its anchor
 // token (an LDS table of the requests' anchors, one probe per record);
 // recycle_score_kernel scores each listed record (one wave per record, fp32
@@ -31,7 +31,7 @@ namespace {
 
 constexpr int kRecRow = 8;  // rollout row: length, up to 6 tokens, padding
 constexpr int kMatchThreads = 256;
-constexpr int kMatchPer = 16;
+constexpr int kMatchPer = 4;  // 65,536 records: 64 workgroups (16: 16 of them, 13.8 us against 8)
 constexpr int kMatchChunk = kMatchThreads * kMatchPer;
 constexpr int kMatchGroup = 64;
 constexpr int kMatchTable = 256;
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void recycle_plan_kernel(
 // One wave per record: lane l takes the 8-column chunks l, l + 64, ... of the
 // row (NI of them hold it), which stays in registers between its norm and the
 // rounding.  VEC: whole 16-byte pieces of every row are aligned.  1,260
-// records of 4,096 bf16 columns (32 trees of 65 slots) 31 -> 14 us against a
+// records of 4,096 bf16 columns (32 trees of 65 slots) 31 -> 13 us against a
 // 256-thread block per record that read each row twice and divided in double.
 template <bool F32, bool VEC, int NI>
 __global__ __launch_bounds__(256) void recycle_keys_kernel(
@@ -183,12 +183,35 @@ __global__ __launch_bounds__(256) void recycle_keys_kernel(
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1)
         ss += __shfl_xor(ss, o, kWave);
+    if constexpr (!F32) {  // unpacked again below, not kept beside the raw pieces
+#pragma unroll
+        for (int i = 0; i < NI; i++)
+            asm volatile("" : "+v"(x[i][0]));
+    }
     const RowScale sc = row_scale(sqrt(ss));
+    uint32_t open = 0;
 #pragma unroll
     for (int i = 0; i < NI; i++) {
         const int c = i * 64 + lane;
-        if (c < ld / 8)
-            dst[c] = unit_chunk_bf16<F32>(x[i], sc);
+        bool near;
+        const u32x4 w = unit_chunk_bf16<F32>(x[i], sc, near);
+        if (c < ld / 8) {
+            dst[c] = w;
+            open |= near ? 1u << i : 0u;
+        }
+    }
+    while (open) {  // the few chunks with a value not decided: settled and stored again
+        const int i = __ffs((int)open) - 1;
+        open &= open - 1;
+        u32x4 y[F32 ? 2 : 1];
+#pragma unroll
+        for (int p = 0; p < (F32 ? 2 : 1); p++) {
+            y[p] = x[0][p];
+#pragma unroll
+            for (int j = 1; j < NI; j++)
+                y[p] = j == i ? x[j][p] : y[p];
+        }
+        dst[i * 64 + lane] = settle_chunk_bf16<F32>(y, sc);
     }
 }
 
@@ -210,10 +233,17 @@ __global__ __launch_bounds__(256) void recycle_wide_keys_kernel(
     }
 }
 
-__global__ void recycle_zero_kernel(int32_t* __restrict__ cnt, int32_t B)
+// One block per request: its query normalised, its match count cleared.
+__global__ __launch_bounds__(1024) void recycle_prep_kernel(const void* __restrict__ queries, int dtype, int32_t d,
+                                                            int32_t ld, uint16_t* __restrict__ qbuf,
+                                                            int32_t* __restrict__ cnt)
 {
-    for (int i = threadIdx.x; i < B; i += blockDim.x)
-        cnt[i] = 0;
+    __shared__ double red[16];
+    const int b = blockIdx.x;
+    if (threadIdx.x == 0)
+        cnt[b] = 0;
+    normalize_row<1024>(queries, dtype, b, d, ld, true, red,
+                        [&](int32_t j, uint16_t bits) { qbuf[(int64_t)b * ld + j] = bits; });
 }
 
 __global__ __launch_bounds__(kMatchThreads) void recycle_match_kernel(
@@ -475,12 +505,8 @@ hipError_t launch_recycle_query(const void* queries, int q_dtype, int32_t B, int
     uint16_t* qbuf = (uint16_t*)ws;
     int32_t* cnt = (int32_t*)(ws + align256((size_t)B * ld * sizeof(uint16_t)));
     int32_t* list = (int32_t*)((char*)cnt + align256((size_t)B * sizeof(int32_t)));
-    hipError_t e = launch_normalize_rows(queries, q_dtype, d, B, B, qbuf, 0, ld, kLayoutRows, 0, 0, nullptr,
-                                         nullptr, nullptr, nullptr, nullptr, nullptr, stream);
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(recycle_zero_kernel, dim3(1), dim3(256), 0, stream, cnt, B);
-    e = hipGetLastError();
+    hipLaunchKernelGGL(recycle_prep_kernel, dim3(B), dim3(1024), 0, stream, queries, q_dtype, d, ld, qbuf, cnt);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
     const int64_t chunks = (capacity + kMatchChunk - 1) / kMatchChunk;

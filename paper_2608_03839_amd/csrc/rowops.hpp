@@ -176,40 +176,41 @@ __device__ __forceinline__ float chunk_value(const u32x4 (&x)[F32 ? 2 : 1], int 
         return __uint_as_float((e & 1) ? x[0][e >> 1] & 0xFFFF0000u : x[0][e >> 1] << 16);
 }
 
-// A chunk's eight bf16 values of the unit row (zeros for a zero or NaN row).
+// A chunk's eight bf16 values of the unit row, and whether some of them need
+// settling (settle_chunk_bf16).
 template <bool F32>
-__device__ __forceinline__ u32x4 unit_chunk_bf16(const u32x4 (&x)[F32 ? 2 : 1], const RowScale& sc)
+__device__ __forceinline__ u32x4 unit_chunk_bf16(const u32x4 (&x)[F32 ? 2 : 1], const RowScale& sc, bool& near)
 {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     u32x4 w;
-    bool near = !sc.fast;
+    near = !sc.fast;
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
         const float q0 = chunk_value<F32>(x, e) * sc.inv, q1 = chunk_value<F32>(x, e + 1) * sc.inv;
         near |= bf16_near(q0) || bf16_near(q1);
         w[e >> 1] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)q0, (__bf16)q1});
     }
-    const bool some = sc.norm > 0.0;
-    if (near && some) {  // rare: some value of this chunk is not decided yet
-        uint32_t open = 0;
+    return w;
+}
+
+// The same with every value settled (zeros for a zero or NaN row).
+template <bool F32>
+__device__ __forceinline__ u32x4 settle_chunk_bf16(const u32x4 (&x)[F32 ? 2 : 1], const RowScale& sc)
+{
+    u32x4 w = {0, 0, 0, 0};
+    if (!(sc.norm > 0.0))
+        return w;
+    for (int e = 0; e < 8; e++) {  // rolled: one copy of the division in double
+        float v = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; e++)
-            open |= (!sc.fast || bf16_near(chunk_value<F32>(x, e) * sc.inv)) ? 1u << e : 0u;
-        while (open) {
-            const int at_e = __ffs((int)open) - 1;
-            open &= open - 1;
-            float v = 0.f;
+        for (int f = 0; f < 8; f++)
+            v = f == e ? chunk_value<F32>(x, f) : v;
+        const uint32_t bits = (uint32_t)unit_bf16(v, sc) << ((e & 1) * 16);
 #pragma unroll
-            for (int e = 0; e < 8; e++)
-                v = e == at_e ? chunk_value<F32>(x, e) : v;
-            const uint32_t bits = bf16_settle(v, v * sc.inv, sc);
-            const int pos = (at_e & 1) * 16;
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                w[q] = q == (at_e >> 1) ? (w[q] & ~(0xFFFFu << pos)) | (bits << pos) : w[q];
-        }
+        for (int q = 0; q < 4; q++)
+            w[q] |= q == (e >> 1) ? bits : 0u;
     }
-    return some ? w : u32x4{0, 0, 0, 0};
+    return w;
 }
 
 // normalize_row for ld <= NT * NV: the row is read once into registers.

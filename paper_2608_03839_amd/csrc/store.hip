@@ -267,44 +267,44 @@ __global__ __launch_bounds__(kRowThreads) void quantize_rows_kernel(
 // other widths load element by element.
 constexpr int kBulkThreads = 512;
 
-// The 16 codes of two chunks of a unit row scaled by 2^shift (s is scaled; zeros
-// for a zero or NaN row).
+// The 16 codes of two chunks of a unit row scaled by 2^shift (s is scaled), and
+// whether some of them need settling (settle_e4m3_16).
 template <bool F32>
-__device__ __forceinline__ u32x4 unit_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1], const RowScale& s, int shift)
+__device__ __forceinline__ u32x4 unit_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1], const RowScale& s, bool& near)
 {
     u32x4 w = {0, 0, 0, 0};
-    auto quotient = [&](int e) { return chunk_value<F32>(x[e >> 3], e & 7) * s.inv; };
-    bool near = !s.fast;
+    near = !s.fast;
 #pragma unroll
     for (int e = 0; e < 16; e += 2) {
-        const float q0 = quotient(e), q1 = quotient(e + 1);
+        const float q0 = chunk_value<F32>(x[e >> 3], e & 7) * s.inv;
+        const float q1 = chunk_value<F32>(x[e >> 3], (e & 7) + 1) * s.inv;
         near |= e4m3_near(q0) || e4m3_near(q1);
         if (e & 2)
             w[e >> 2] = __builtin_amdgcn_cvt_pk_fp8_f32(q0, q1, w[e >> 2], true);
         else
             w[e >> 2] = __builtin_amdgcn_cvt_pk_fp8_f32(q0, q1, w[e >> 2], false);
     }
-    const bool some = s.norm > 0.0;
-    if (near && some) {  // rare: some value of the two chunks is not decided yet
-        uint32_t open = 0;
+    return w;
+}
+
+// The same with every value settled (zeros for a zero or NaN row).
+template <bool F32>
+__device__ __forceinline__ u32x4 settle_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1], const RowScale& s, int shift)
+{
+    u32x4 w = {0, 0, 0, 0};
+    if (!(s.norm > 0.0))
+        return w;
+    for (int e = 0; e < 16; e++) {  // rolled: one copy of the division in double
+        float v = 0.f;
 #pragma unroll
-        for (int e = 0; e < 16; e++)
-            open |= (!s.fast || e4m3_near(quotient(e))) ? 1u << e : 0u;
-        while (open) {
-            const int at_e = __ffs((int)open) - 1;
-            open &= open - 1;
-            float v = 0.f;
+        for (int f = 0; f < 16; f++)
+            v = f == e ? chunk_value<F32>(x[f >> 3], f & 7) : v;
+        const uint32_t bits = (uint32_t)unit_e4m3(v, s, shift) << ((e & 3) * 8);
 #pragma unroll
-            for (int e = 0; e < 16; e++)
-                v = e == at_e ? chunk_value<F32>(x[e >> 3], e & 7) : v;
-            const uint32_t bits = e4m3_settle(v, v * s.inv, s, shift);
-            const int pos = (at_e & 3) * 8;
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                w[q] = q == (at_e >> 2) ? (w[q] & ~(0xFFu << pos)) | (bits << pos) : w[q];
-        }
+        for (int q = 0; q < 4; q++)
+            w[q] |= q == (e >> 2) ? bits : 0u;
     }
-    return some ? w : u32x4{0, 0, 0, 0};
+    return w;
 }
 
 template <int FMT, bool F32, bool VEC, int NI, int R>
@@ -392,20 +392,45 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4)
     }
     uint8_t* base = out + (dst >> 5) * rs;
     const int row32 = (int)(dst & 31);
-#pragma unroll
-    for (int i = 0; i < NI; i++) {
+    auto put = [&](int i, const u32x4& w) {
         const int u = u0 + i * kUnits;
-        if (u >= units)
-            break;
-        u32x4 w;  // the unit's 16 stored bytes
-        if constexpr (FMT == kKeyFp8)
-            w = unit_e4m3_16<F32>(x[i], sc, shift);
-        else
-            w = unit_chunk_bf16<F32>(x[i][0], sc);
         // 16-byte slot of (row, unit) in its 4 KiB tile
         const int slot = FMT == kKeyFp8 ? ((u & 7) >> 1) * 64 + row32 + 32 * (u & 1)
                                         : (u & 3) * 64 + row32 + 32 * ((u & 7) >> 2);
         *(u32x4*)(base + (int64_t)(u >> 3) * ws + slot * 16) = w;
+    };
+    // the decided units first; the few others are then settled and stored again
+    uint32_t open = 0;
+#pragma unroll
+    for (int i = 0; i < NI; i++) {
+        if (u0 + i * kUnits >= units)
+            break;
+        bool near;
+        u32x4 w;
+        if constexpr (FMT == kKeyFp8)
+            w = unit_e4m3_16<F32>(x[i], sc, near);
+        else
+            w = unit_chunk_bf16<F32>(x[i][0], sc, near);
+        put(i, w);
+        open |= near ? 1u << i : 0u;
+    }
+    while (open) {
+        const int i = __ffs((int)open) - 1;
+        open &= open - 1;
+        u32x4 y[H][F32 ? 2 : 1];
+#pragma unroll
+        for (int h = 0; h < H; h++)
+#pragma unroll
+            for (int p = 0; p < (F32 ? 2 : 1); p++) {
+                y[h][p] = x[0][h][p];
+#pragma unroll
+                for (int j = 1; j < NI; j++)
+                    y[h][p] = j == i ? x[j][h][p] : y[h][p];
+            }
+        if constexpr (FMT == kKeyFp8)
+            put(i, settle_e4m3_16<F32>(y, sc, shift));
+        else
+            put(i, settle_chunk_bf16<F32>(y[0], sc));
     }
     if (u0 == 0) {  // one lane per row
         if constexpr (FMT == kKeyFp8)
