@@ -148,6 +148,10 @@ int32_t query_topk_enqueue(const oil_pool* pool, const void* queries, int32_t q_
                 g_timer.used++;
         }
     }
+    if (FS && oil::topk_scored(n_valid))
+        return hip_status(e != hipSuccess ? e
+                                          : oil::launch_topk_scored(G, w.g_ld, n_valid, B, k, scores, idx, st, FS,
+                                                                    w.fs_ld));
     const uint64_t* chosen = nullptr;
     if (e == hipSuccess)
         e = oil::launch_topk_blocks(G, w.g_ld, n_valid, B, k, ca, cb, &chosen, st);

@@ -170,6 +170,44 @@ __global__ __launch_bounds__(kSelThreads) void topk_merge_kernel(
         cand_out[((int64_t)b * n_out + g) * k + threadIdx.x] = sh.sel[threadIdx.x];
 }
 
+// The scores of k chosen row blocks (first_row[g] their first positions, -1:
+// none; by position, or 32 per slot) -> the k best positions, ranked.  VPT *
+// 256 >= k * 32.
+template <int VPT>
+__device__ void final_select(const int64_t* first_row, int k, const float* __restrict__ sc, bool by_position,
+                             int64_t n_valid, SelShared& sh, float* __restrict__ os, int32_t* __restrict__ oi)
+{
+    const int t = threadIdx.x;
+    uint64_t v[VPT];
+#pragma unroll
+    for (int j = 0; j < VPT; j++) {
+        const int slot = j * kSelThreads + t;
+        const int g = slot / kRowBlock;
+        v[j] = 0ull;
+        if (g < k && first_row[g] >= 0) {
+            const int64_t row = first_row[g] + slot % kRowBlock;
+            if (row < n_valid)
+                v[j] = rank_key(sc[by_position ? row : slot], (uint32_t)row);
+        }
+    }
+    block_select(v, k, sh);
+    if (t < k) {
+        const uint64_t me = sh.sel[t];
+        int rank = 0;
+        for (int j = 0; j < k; j++) {
+            const uint64_t o = sh.sel[j];
+            rank += (o > me) || (o == me && j < t);
+        }
+        if (me == 0) {
+            os[rank] = -INFINITY;
+            oi[rank] = -1;
+        } else {
+            os[rank] = code_score((uint32_t)(me >> 32));
+            oi[rank] = (int32_t)key_pos(me);
+        }
+    }
+}
+
 // Step 3: the 32 rescored scores of each of the k chosen row blocks -> the k
 // best positions, ranked (descending; equal keys, i.e. padding, in slot order).
 // VPT * 256 >= k * 32.
@@ -186,37 +224,41 @@ __global__ __launch_bounds__(kSelThreads) void topk_final_kernel(
         first_row[t] = bk ? (int64_t)(key_pos(bk) / kRowBlock) * kRowBlock : -1;
     }
     __syncthreads();
-    const float* sc = SC + (int64_t)b * k * kRowBlock;
-    uint64_t v[VPT];
+    final_select<VPT>(first_row, k, FS ? FS + b * fs_ld : SC + (int64_t)b * k * kRowBlock, FS != nullptr, n_valid, sh,
+                      out_s + (int64_t)b * k, out_i + (int64_t)b * k);
+}
+
+// Steps 1 and 3 in one launch, for scans that wrote every score: one workgroup
+// per query selects the k best of all its block keys (at most VPT * 256) and
+// then the k best of those blocks' scores.  A separate launch for each
+// cost a launch and its gap more (65,536 x 4,096, one query, k = 16: 6.2 + 5.6 us
+// and a gap against 9).
+template <int VPT, int FVPT>
+__global__ __launch_bounds__(kSelThreads) void topk_scored_kernel(const uint64_t* __restrict__ G, int64_t g_ld,
+                                                                  int64_t n_rb, int k, int64_t n_valid,
+                                                                  float* __restrict__ out_s,
+                                                                  int32_t* __restrict__ out_i,
+                                                                  const float* __restrict__ FS, int64_t fs_ld)
+{
+    __shared__ SelShared sh;
+    __shared__ int64_t first_row[OIL_TOPK_MAX];
+    const int b = blockIdx.x, t = threadIdx.x;
+    {
+        const uint64_t* row = G + (int64_t)b * g_ld;
+        uint64_t v[VPT];
 #pragma unroll
-    for (int j = 0; j < VPT; j++) {
-        const int slot = j * kSelThreads + t;
-        const int g = slot / kRowBlock;
-        v[j] = 0ull;
-        if (g < k && first_row[g] >= 0) {
-            const int64_t row = first_row[g] + slot % kRowBlock;
-            if (row < n_valid)
-                v[j] = rank_key(FS ? FS[b * fs_ld + row] : sc[slot], (uint32_t)row);
+        for (int j = 0; j < VPT; j++) {
+            const int64_t at = j * kSelThreads + t;
+            v[j] = at < n_rb ? row[at] : 0ull;
         }
+        block_select(v, k, sh);
     }
-    block_select(v, k, sh);
     if (t < k) {
-        const uint64_t me = sh.sel[t];
-        int rank = 0;
-        for (int j = 0; j < k; j++) {
-            const uint64_t o = sh.sel[j];
-            rank += (o > me) || (o == me && j < t);
-        }
-        float* os = out_s + (int64_t)b * k;
-        int32_t* oi = out_i + (int64_t)b * k;
-        if (me == 0) {
-            os[rank] = -INFINITY;
-            oi[rank] = -1;
-        } else {
-            os[rank] = code_score((uint32_t)(me >> 32));
-            oi[rank] = (int32_t)key_pos(me);
-        }
+        const uint64_t bk = sh.sel[t];
+        first_row[t] = bk ? (int64_t)(key_pos(bk) / kRowBlock) * kRowBlock : -1;
     }
+    __syncthreads();
+    final_select<FVPT>(first_row, k, FS + b * fs_ld, true, n_valid, sh, out_s + (int64_t)b * k, out_i + (int64_t)b * k);
 }
 
 int64_t topk_chunks(int64_t n) { return n <= 0 ? 1 : (n + kBlkSpan - 1) / kBlkSpan; }
@@ -272,6 +314,31 @@ hipError_t launch_topk_blocks(const uint64_t* G, int64_t g_ld, int64_t n_valid, 
     }
     *chosen = src;
     return e;
+}
+
+// Block keys up to which one workgroup per query takes the whole selection.
+constexpr int kScoredSpan = kSelSpan;
+
+bool topk_scored(int64_t n_valid) { return (n_valid + kRowBlock - 1) / kRowBlock <= kScoredSpan; }
+
+hipError_t launch_topk_scored(const uint64_t* G, int64_t g_ld, int64_t n_valid, int32_t B, int32_t k, float* out_s,
+                              int32_t* out_i, hipStream_t stream, const float* full_scores, int64_t fs_ld)
+{
+    const int64_t n_rb = (n_valid + kRowBlock - 1) / kRowBlock;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(B), dim3(kSelThreads), 0, stream, G, g_ld, n_rb, k, n_valid, out_s, out_i,
+                           full_scores, fs_ld);
+    };
+    const bool small = k * kRowBlock <= kSelThreads * 4;
+    if (n_rb <= kSelThreads * 1)
+        small ? go(topk_scored_kernel<1, 4>) : go(topk_scored_kernel<1, kFinalVpt>);
+    else if (n_rb <= kSelThreads * 4)
+        small ? go(topk_scored_kernel<4, 4>) : go(topk_scored_kernel<4, kFinalVpt>);
+    else if (n_rb <= kSelThreads * 8)
+        small ? go(topk_scored_kernel<8, 4>) : go(topk_scored_kernel<8, kFinalVpt>);
+    else
+        small ? go(topk_scored_kernel<kSelVpt, 4>) : go(topk_scored_kernel<kSelVpt, kFinalVpt>);
+    return hipGetLastError();
 }
 
 hipError_t launch_topk_final(const uint64_t* chosen, int32_t B, int32_t k, const float* SC,
