@@ -397,7 +397,7 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4)
         // 16-byte slot of (row, unit) in its 4 KiB tile
         const int slot = FMT == kKeyFp8 ? ((u & 7) >> 1) * 64 + row32 + 32 * (u & 1)
                                         : (u & 3) * 64 + row32 + 32 * ((u & 7) >> 2);
-        *(u32x4*)(base + (int64_t)(u >> 3) * ws + slot * 16) = w;
+        __builtin_nontemporal_store(w, (u32x4*)(base + (int64_t)(u >> 3) * ws + slot * 16));
     };
     // the decided units first; the few others are then settled and stored again
     uint32_t open = 0;
