@@ -157,7 +157,7 @@ int32_t query_topk_enqueue(const oil_pool* pool, const void* queries, int32_t q_
         e = oil::launch_topk_blocks(G, w.g_ld, n_valid, B, k, ca, cb, &chosen, st);
     if (e == hipSuccess && !FS)
         e = oil::launch_rescore(pool->keys, pool->ld, pool->rs, pool->ws, n_valid, qbuf, B, chosen, k,
-                                pool->prompts, exclude_prompt, SC, st, pool->fmt, pool->kscale, qscale);
+                                pool->prompts, exclude_prompt, SC, st, pool->fmt, pool->kscale, qscale, G, w.g_ld);
     if (e == hipSuccess)
         e = oil::launch_topk_final(chosen, B, k, SC, n_valid, scores, idx, st, FS, w.fs_ld);
     return hip_status(e);

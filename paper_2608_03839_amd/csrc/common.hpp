@@ -96,4 +96,28 @@ __device__ __forceinline__ uint64_t rank_key(float s, uint32_t pos)
 
 __device__ __forceinline__ uint32_t key_pos(uint64_t key) { return 0xFFFFFFFFu - (uint32_t)key; }
 
+// Block word: what the scan keeps of a (query, 32-row block).  High 32 bits: the
+// best score's code; bits 5 .. 31: the upper 27 bits of the runner-up's code (0:
+// none); bits 0 .. 4: the best row in the block (the first of equal ones).  0: no
+// position.  With the block's number the high word and the row make the best
+// row's rank key.
+__device__ __forceinline__ uint64_t block_word(uint32_t best, uint32_t runner, int row)
+{
+    return best ? ((uint64_t)best << 32) | (runner & ~31u) | (uint32_t)row : 0ull;
+}
+
+__device__ __forceinline__ uint64_t word_key(uint64_t word, int64_t block)
+{
+    return word ? (word & 0xFFFFFFFF00000000ull) | (0xFFFFFFFFu - ((uint32_t)block * 32u + ((uint32_t)word & 31u)))
+                : 0ull;
+}
+
+// The runner-up's code is at least / at most this.
+__device__ __forceinline__ uint32_t word_runner_low(uint64_t word) { return (uint32_t)word & ~31u; }
+__device__ __forceinline__ uint32_t word_runner_high(uint64_t word)
+{
+    const uint32_t c = (uint32_t)word & ~31u;
+    return c ? c | 31u : 0u;
+}
+
 }  // namespace oil

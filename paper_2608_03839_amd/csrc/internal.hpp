@@ -64,8 +64,8 @@ hipError_t launch_scan(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws,
 hipError_t launch_rescore(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
                           const void* qbuf, int32_t B, const uint64_t* blocks, int32_t k,
                           const int32_t* prompt, const int32_t* exclude, float* SC,
-                          hipStream_t stream, int fmt = kKeyBf16, const float* kscale = nullptr,
-                          const float* qscale = nullptr);
+                          hipStream_t stream, int fmt, const float* kscale, const float* qscale,
+                          const uint64_t* G, int64_t g_ld);
 // Quantize raw rows to the fp8 store format (normalise in double, per-row
 // power-of-two scale putting the largest magnitude in [128, 256), E4M3
 // nearest-even) into 4 KiB fp8 tiles (rs_bytes, ws_bytes) or rows.

@@ -1,9 +1,10 @@
 // Pool scan: s[b][i] = q_b . k_i for every stored position i < n_valid
 // (Algorithm 1 retrieve step; with unit operands this is cos(h_t, h_i)).
 // bf16 operands, fp32 accumulation.  The key pool is read exactly once per
-// call.  The scan keeps, per (query, 32-row block), only the block's best
-// (score, position) key; the top-k passes pick the k best blocks per query
-// and the rescore kernels below recompute those blocks' 32 scores with the
+// call.  The scan keeps, per (query, 32-row block), only one word: the block's
+// best score and row, and a bound on its runner-up (block_word); the top-k
+// passes pick the k best blocks per query and the rescore kernel below
+// recomputes the 32 scores of those that can hold a second hit, with the
 // scan's own instruction sequence (bit-identical values).  Writing every
 // score (B x N x 4 bytes) interleaves a large store stream with the key reads
 // and costs far more than its bytes; re-reading k blocks per query does not.
@@ -79,10 +80,15 @@
 #ifndef OIL_FP8_PF
 #define OIL_FP8_PF 1
 #endif
-// Prefetch depth (windows in flight per wave) of the MFMA rescore.  At 1M x
-// 4096, B = k = 32 (1024 waves, one per SIMD): depth 0 73 us, 1 45, 2 46, 3 47.5.
+// Prefetch depth (windows in flight per wave) of the MFMA rescore, whose few
+// remaining waves are chains of loads: full draft step (524,288 x 8,192, 64
+// queries) 55 / 41 / 38 us at depth 1 / 3 / 5, 1M x 4,096, 32 queries 36 / 34 /
+// 37; fp8 keys (half as many windows) 21.5 / 22.6 / 25.2.
 #ifndef OIL_RESCORE_PF
-#define OIL_RESCORE_PF 1
+#define OIL_RESCORE_PF 3
+#endif
+#ifndef OIL_RESCORE_PF8
+#define OIL_RESCORE_PF8 1
 #endif
 // Windows in flight per wave of the remainder launch of the B <= 64 scan,
 // for one and two query tiles.
@@ -167,6 +173,38 @@ __device__ __forceinline__ void store_tile_scores(float* __restrict__ fs, const 
 #pragma unroll
     for (int i = 0; i < 4; i++)
         *(floatx4*)(fs + i * 8 + h * 4) = floatx4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
+}
+
+// A (query, row block)'s block word from the block's MFMA tile: v[e], the score
+// of row 8 (e / 4) + 4 h + e % 4 of the tile, is scaled (fp8: exact, powers of
+// two) and masked in place; both lanes of the query get the word (see
+// block_word).
+template <int FMT>
+__device__ __forceinline__ uint64_t tile_word(floatx16& v, const float (&ks)[16], float qs, const int32_t (&pr)[16],
+                                              int32_t ex, int64_t row0, int h, int64_t n_valid)
+{
+    const int left = (int)(n_valid - row0 < kRowBlock ? n_valid - row0 : kRowBlock);
+    uint32_t c1 = 0, c2 = 0;
+    int row = 0;
+#pragma unroll
+    for (int e = 0; e < 16; e++) {
+        const int r = (e / 4) * 8 + h * 4 + e % 4;
+        float s = v[e];
+        if constexpr (FMT == kKeyFp8)
+            s = s * (ks[e] * qs);
+        if (ex >= 0 && pr[e] == ex)
+            s = __uint_as_float(kNoScoreBits);
+        v[e] = s;
+        const uint32_t c = r < left ? score_code(s) : 0u;
+        c2 = max(c2, min(c, c1));
+        row = c > c1 ? r : row;
+        c1 = max(c1, c);
+    }
+    const uint32_t o1 = __shfl_xor(c1, 32, kWave), o2 = __shfl_xor(c2, 32, kWave);
+    const int orow = __shfl_xor(row, 32, kWave);
+    c2 = max(max(c2, o2), min(c1, o1));
+    row = (o1 > c1 || (o1 == c1 && orow < row)) ? orow : row;
+    return block_word(max(c1, o1), c2, row);
 }
 
 // ----------------------------------------------------------------- GEMV (B <= 4)
@@ -258,8 +296,8 @@ __global__ __launch_bounds__(256) void scan_gemv_kernel(
                 const uint64_t other = __shfl_xor(best, o, kWave);
                 best = other > best ? other : best;
             }
-            if (lane == 0)
-                G[b * g_ld + rb] = best;
+            if (lane == 0)  // every score is written: no runner-up is asked for
+                G[b * g_ld + rb] = best ? block_word((uint32_t)(best >> 32), 0u, (int)(key_pos(best) % kRowBlock)) : 0ull;
         };
         if constexpr (SPLIT) {
             // the waves' parts meet in LDS and wave b finishes query b (the
@@ -425,26 +463,9 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(
             tile_rows_load(pr, prompt, rb * kRowBlock, h, n_valid);
 #pragma unroll
         for (int nt = 0; nt < NT; nt++) {
-            uint64_t best = 0;
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int64_t row = rb * kRowBlock + (e / 4) * 8 + h * 4 + e % 4;
-                if (row < n_valid) {
-                    float v = acc[mt][nt][e];
-                    if constexpr (FMT == kKeyFp8)
-                        v = v * (ks[e] * qs[nt]);  // powers of two: exact
-                    if (ex[nt] >= 0 && pr[e] == ex[nt])
-                        v = __uint_as_float(kNoScoreBits);
-                    if constexpr (FULL)
-                        acc[mt][nt][e] = v;
-                    const uint64_t key = rank_key(v, (uint32_t)row);
-                    best = key > best ? key : best;
-                }
-            }
+            const uint64_t best = tile_word<FMT>(acc[mt][nt], ks, qs[nt], pr, ex[nt], rb * kRowBlock, h, n_valid);
             if (FULL && FS && nt * 32 + r < B && rb < n_rb)
                 store_tile_scores(FS + (nt * 32 + r) * fs_ld + rb * kRowBlock, acc[mt][nt], h);
-            const uint64_t other = __shfl_xor(best, 32, kWave);
-            best = other > best ? other : best;
             if (h == 0)
                 gk[wave][nt * 32 + r][mt] = best;
         }
@@ -522,13 +543,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2
 #pragma unroll
             for (int nt = 0; nt < NT; nt++)
                 acc[mt][nt] = floatx16{};
+        // the next group's tiles: picked by a select in the loop (a branch there
+        // splits the pipelined loop into blocks that wait for their own loads:
+        // 1,215 -> 1,237 us)
+        int64_t nxt[MT];
+        tiles_of(g + stride < n_groups ? g + stride : g, nxt);
         for (int w0 = 0; w0 < nwin; w0 += NS) {
 #pragma unroll
             for (int u = 0; u < NS; u++) {
                 const int wl = w0 + u + 1;
-                if (wl == nwin)  // the next group's tiles (this group's loads are all issued)
-                    tiles_of(g + stride < n_groups ? g + stride : g, cur);
-                load(a[(u + 1) % NS], b[(u + 1) % NS], cur, wl < nwin ? wl : 0);
+                int64_t at[MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; mt++)
+                    at[mt] = wl < nwin ? cur[mt] : nxt[mt];
+                load(a[(u + 1) % NS], b[(u + 1) % NS], at, wl < nwin ? wl : 0);
                 if constexpr (FMT == kKeyFp8) {
 #pragma unroll
                     for (int s = 0; s < 4; s += 2)
@@ -549,6 +577,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2
                 }
             }
         }
+#pragma unroll
+        for (int mt = 0; mt < MT; mt++)
+            cur[mt] = nxt[mt];
         // block keys of group g, as in scan_mfma_kernel
         const int64_t rbb = g * 4 * MT;
         const int64_t rb0 = rbb + wave * MT;
@@ -572,22 +603,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2
                 tile_rows_load(pr, prompt, rb * kRowBlock, h, n_valid);
 #pragma unroll
             for (int nt = 0; nt < NT; nt++) {
-                uint64_t best = 0;
-#pragma unroll
-                for (int e = 0; e < 16; e++) {
-                    const int64_t row = rb * kRowBlock + (e / 4) * 8 + h * 4 + e % 4;
-                    if (row < n_valid) {
-                        float v = acc[mt][nt][e];
-                        if constexpr (FMT == kKeyFp8)
-                            v = v * (ks[e] * qs[nt]);
-                        if (ex[nt] >= 0 && pr[e] == ex[nt])
-                            v = __uint_as_float(kNoScoreBits);
-                        const uint64_t key = rank_key(v, (uint32_t)row);
-                        best = key > best ? key : best;
-                    }
-                }
-                const uint64_t other = __shfl_xor(best, 32, kWave);
-                best = other > best ? other : best;
+                const uint64_t best = tile_word<FMT>(acc[mt][nt], ks, qs[nt], pr, ex[nt], rb * kRowBlock, h, n_valid);
                 if (h == 0)
                     gk[wave][nt * 32 + r][mt] = best;
             }
@@ -901,26 +917,9 @@ scan_mfma_wide_kernel(
             // the tile moves out of the accumulation registers here, one tile at a time
             floatx16 t = acc[mt][nt];
             asm volatile("" : "+v"(t));
-            uint64_t best = 0;
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int64_t row = rb * kRowBlock + (e / 4) * 8 + h * 4 + e % 4;
-                if (row < n_valid) {
-                    float v = t[e];
-                    if constexpr (FMT == kKeyFp8)
-                        v = v * (ks[e] * qs[nt]);  // powers of two: exact, as the narrow scan scales it
-                    if (ex[nt] >= 0 && pr[e] == ex[nt])
-                        v = __uint_as_float(kNoScoreBits);
-                    if constexpr (FULL)
-                        t[e] = v;
-                    const uint64_t key = rank_key(v, (uint32_t)row);
-                    best = key > best ? key : best;
-                }
-            }
+            const uint64_t best = tile_word<FMT>(t, ks, qs[nt], pr, ex[nt], rb * kRowBlock, h, n_valid);
             if (FULL && FS && qb < B && rb < n_rb)
                 store_tile_scores(FS + qb * fs_ld + rb * kRowBlock, t, h);
-            const uint64_t other = __shfl_xor(best, 32, kWave);
-            best = other > best ? other : best;
             // streamed past the caches up to four query tiles (B = 128: 1.498
             // -> 1.460 ms); plain stores at 8 and 16 tiles, whose block keys
             // are 2-4x as many (B = 256 / 512: 2.11 / 3.63 ms against 2.18 /
@@ -1087,25 +1086,9 @@ __global__ __launch_bounds__(64 * (NT + 4)) void scan_tail_kernel(
         tile_rows_load(pr, prompt, rb * kRowBlock, h, n_valid);
     if constexpr (FMT == kKeyFp8)
         tile_rows_load(ks, kscale, rb * kRowBlock, h, n_valid);
-    uint64_t best = 0;
-#pragma unroll
-    for (int e = 0; e < 16; e++) {
-        const int64_t row = rb * kRowBlock + (e / 4) * 8 + h * 4 + e % 4;
-        if (row < n_valid) {
-            float v = acc[e];
-            if constexpr (FMT == kKeyFp8)
-                v = v * (ks[e] * qs);  // powers of two: exact
-            if (ex >= 0 && pr[e] == ex)
-                v = __uint_as_float(kNoScoreBits);
-            acc[e] = v;
-            const uint64_t key = rank_key(v, (uint32_t)row);
-            best = key > best ? key : best;
-        }
-    }
+    const uint64_t best = tile_word<FMT>(acc, ks, qs, pr, ex, rb * kRowBlock, h, n_valid);
     if (FS && qlive)
         store_tile_scores(FS + qb * fs_ld + rb * kRowBlock, acc, h);
-    const uint64_t other = __shfl_xor(best, 32, kWave);
-    best = other > best ? other : best;
     if (qlive && h == 0)
         __builtin_nontemporal_store(best, &G[qb * g_ld + rb]);
 }
@@ -1115,6 +1098,13 @@ __global__ __launch_bounds__(64 * (NT + 4)) void scan_tail_kernel(
 // (0: no block, the slot's scores are "no position").  Scores land in
 // SC[(query * k + slot) * 32 + row in block].
 
+// Only blocks that can hold a second row of the k best are read again: a block
+// whose runner-up lies below a score that k positions are known to reach
+// adds its best row alone, and that score is in its word (full draft step: 172
+// -> 41 us; 1M x 4,096, 512 queries, fp8 keys: 323 -> 161).  The runner-up's 27
+// bits take the place of the position's upper ones in the block word, so the
+// scan stores no more than before.
+//
 // MFMA path: the same v_mfma_f32_32x32x16_bf16 sequence as the scan (windows
 // in order, sub-steps in order, starting from zero) on the block's tile and
 // the query's 32-query fragment tile, so element (row, query) is bit-identical
@@ -1124,18 +1114,40 @@ __global__ __launch_bounds__(64) void rescore_mfma_kernel(
     const uint16_t* __restrict__ keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
     const bf16x8* __restrict__ qfrag, int n_qtiles, const uint64_t* __restrict__ blocks, int k,
     const int32_t* __restrict__ prompt, const int32_t* __restrict__ exclude, float* __restrict__ SC,
-    const float* __restrict__ kscale, const float* __restrict__ qscale)
+    const float* __restrict__ kscale, const float* __restrict__ qscale, const uint64_t* __restrict__ G, int64_t g_ld)
 {
     constexpr int NS = PF + 1;
     const int slot = blockIdx.x, qb = blockIdx.y, lane = threadIdx.x;
     const int h = lane >> 5, r = lane & 31;
     float* out = SC + ((int64_t)qb * k + slot) * kRowBlock;
-    const uint64_t bk = blocks[(int64_t)qb * k + slot];
-    const int64_t rb = key_pos(bk) / kRowBlock;
-    // no block (or, defensively, one past the pool: nothing is read there)
-    if (bk == 0 || rb * kRowBlock >= n_valid) {
+    // lane j: the j-th chosen block's key and word.  cut is the k-th largest code
+    // among the blocks' best rows and what their runners-up reach at least: k
+    // positions have it, so no position below it is among the k best.
+    const uint64_t keyj = lane < k ? blocks[(int64_t)qb * k + lane] : 0ull;
+    const int64_t rbj = key_pos(keyj) / kRowBlock;
+    const uint64_t wordj = keyj && rbj * kRowBlock < n_valid ? G[qb * g_ld + rbj] : 0ull;
+    const uint32_t c1 = (uint32_t)(wordj >> 32), c2 = word_runner_low(wordj);
+    int n1 = 0, n2 = 0;  // values above this lane's two (equal ones by lane, best rows first)
+    for (int j = 0; j < k; j++) {
+        const uint32_t o1 = __builtin_amdgcn_readlane(c1, j), o2 = __builtin_amdgcn_readlane(c2, j);
+        n1 += (o1 > c1 || (o1 == c1 && j < lane)) + (o2 > c1);
+        n2 += (o1 >= c2) + (o2 > c2 || (o2 == c2 && j < lane));
+    }
+    // exactly one of the 2 k values has k - 1 before it
+    const uint64_t m1 = __ballot(lane < k && n1 == k - 1), m2 = __ballot(lane < k && n2 == k - 1);
+    const uint32_t cut = m1 ? __builtin_amdgcn_readlane(c1, __ffsll((unsigned long long)m1) - 1)
+                            : m2 ? __builtin_amdgcn_readlane(c2, __ffsll((unsigned long long)m2) - 1) : 0u;
+    const uint32_t high = __builtin_amdgcn_readlane((uint32_t)(wordj >> 32), slot);
+    const uint32_t low = __builtin_amdgcn_readlane((uint32_t)wordj, slot);
+    const uint64_t word = ((uint64_t)high << 32) | low;
+    const int64_t rb = (int64_t)__builtin_amdgcn_readlane((uint32_t)rbj, slot);
+    // no block (or, defensively, one past the pool: nothing is read there), or
+    // one whose other rows are all below the cut: its best row alone, as its
+    // word holds it
+    if (word == 0 || word_runner_high(word) < cut) {
         if (lane < kRowBlock)
-            out[lane] = __uint_as_float(kNoScoreBits);
+            out[lane] = word && lane == (int)(word & 31) ? code_score((uint32_t)(word >> 32))
+                                                         : __uint_as_float(kNoScoreBits);
         return;
     }
     const int t = qb >> 5, n = qb & 31;
@@ -1557,17 +1569,17 @@ hipError_t launch_scan(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws,
 hipError_t launch_rescore(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
                           const void* qbuf, int32_t B, const uint64_t* blocks, int32_t k,
                           const int32_t* prompt, const int32_t* exclude, float* SC, hipStream_t stream,
-                          int fmt, const float* kscale, const float* qscale)
+                          int fmt, const float* kscale, const float* qscale, const uint64_t* G, int64_t g_ld)
 {
     const dim3 g((unsigned)k, (unsigned)B);
     if (fmt == kKeyFp8)
-        hipLaunchKernelGGL((rescore_mfma_kernel<OIL_RESCORE_PF, kKeyFp8>), g, dim3(64), 0, stream, keys, ld, rs, ws, n_valid,
+        hipLaunchKernelGGL((rescore_mfma_kernel<OIL_RESCORE_PF8, kKeyFp8>), g, dim3(64), 0, stream, keys, ld, rs, ws, n_valid,
                            (const bf16x8*)qbuf, scan_query_tiles(B), blocks, k, prompt, exclude, SC, kscale,
-                           qscale);
+                           qscale, G, g_ld);
     else
         hipLaunchKernelGGL((rescore_mfma_kernel<OIL_RESCORE_PF, kKeyBf16>), g, dim3(64), 0, stream, keys, ld, rs, ws, n_valid,
                            (const bf16x8*)qbuf, scan_query_tiles(B), blocks, k, prompt, exclude, SC, nullptr,
-                           nullptr);
+                           nullptr, G, g_ld);
     return hipGetLastError();
 }
 

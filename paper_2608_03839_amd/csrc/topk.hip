@@ -126,6 +126,27 @@ __device__ void block_select(const uint64_t (&v)[VPT], int k, SelShared& sh)
     __syncthreads();
 }
 
+// Rank keys of the block words base + thread, base + thread + 256, ... of a
+// query's n_rb: every load first, at clamped addresses (a load under a condition
+// of its own is waited for before the next; an empty pool's first word is in
+// the workspace too, and not used).
+template <int VPT>
+__device__ __forceinline__ void load_keys(uint64_t (&v)[VPT], const uint64_t* __restrict__ row, int64_t base,
+                                          int64_t n_rb)
+{
+    const int64_t last = n_rb > 0 ? n_rb - 1 : 0;
+#pragma unroll
+    for (int j = 0; j < VPT; j++) {
+        const int64_t at = base + j * kSelThreads + threadIdx.x;
+        v[j] = row[at < last ? at : last];
+    }
+#pragma unroll
+    for (int j = 0; j < VPT; j++) {
+        const int64_t at = base + j * kSelThreads + threadIdx.x;
+        v[j] = at < n_rb ? word_key(v[j], at) : 0ull;
+    }
+}
+
 // Step 1, first level: block keys -> k candidates per chunk of VPT * 256 keys.
 template <int VPT>
 __global__ __launch_bounds__(kSelThreads) void topk_blocks_kernel(
@@ -137,11 +158,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_blocks_kernel(
     const int64_t base = (int64_t)c * (kSelThreads * VPT);
     const uint64_t* row = G + (int64_t)b * g_ld;
     uint64_t v[VPT];
-#pragma unroll
-    for (int j = 0; j < VPT; j++) {
-        const int64_t at = base + j * kSelThreads + threadIdx.x;
-        v[j] = at < n_rb ? row[at] : 0ull;
-    }
+    load_keys(v, row, base, n_rb);
     block_select(v, k, sh);
     if (threadIdx.x < k)
         cand[((int64_t)b * n_chunks + c) * k + threadIdx.x] = sh.sel[threadIdx.x];
@@ -173,23 +190,27 @@ __global__ __launch_bounds__(kSelThreads) void topk_merge_kernel(
 // The scores of k chosen row blocks (first_row[g] their first positions, -1:
 // none; by position, or 32 per slot) -> the k best positions, ranked.  VPT *
 // 256 >= k * 32.
-template <int VPT>
-__device__ void final_select(const int64_t* first_row, int k, const float* __restrict__ sc, bool by_position,
-                             int64_t n_valid, SelShared& sh, float* __restrict__ os, int32_t* __restrict__ oi)
+template <int VPT, bool BY_POSITION>
+__device__ void final_select(const int64_t* first_row, int k, const float* __restrict__ sc, int64_t n_valid,
+                             SelShared& sh, float* __restrict__ os, int32_t* __restrict__ oi)
 {
     const int t = threadIdx.x;
     uint64_t v[VPT];
+    float x[VPT];
+    int64_t at[VPT];  // the slot's position, -1: none
 #pragma unroll
     for (int j = 0; j < VPT; j++) {
         const int slot = j * kSelThreads + t;
-        const int g = slot / kRowBlock;
-        v[j] = 0ull;
-        if (g < k && first_row[g] >= 0) {
-            const int64_t row = first_row[g] + slot % kRowBlock;
-            if (row < n_valid)
-                v[j] = rank_key(sc[by_position ? row : slot], (uint32_t)row);
-        }
+        const int64_t first = slot < k * kRowBlock ? first_row[slot / kRowBlock] : -1;
+        const int64_t row = first + slot % kRowBlock;
+        at[j] = first >= 0 && row < n_valid ? row : -1;
     }
+#pragma unroll
+    for (int j = 0; j < VPT; j++)  // every load first: the first score where there is none to read
+        x[j] = sc[at[j] < 0 ? 0 : BY_POSITION ? at[j] : j * kSelThreads + t];
+#pragma unroll
+    for (int j = 0; j < VPT; j++)
+        v[j] = at[j] >= 0 ? rank_key(x[j], (uint32_t)at[j]) : 0ull;
     block_select(v, k, sh);
     if (t < k) {
         const uint64_t me = sh.sel[t];
@@ -224,8 +245,12 @@ __global__ __launch_bounds__(kSelThreads) void topk_final_kernel(
         first_row[t] = bk ? (int64_t)(key_pos(bk) / kRowBlock) * kRowBlock : -1;
     }
     __syncthreads();
-    final_select<VPT>(first_row, k, FS ? FS + b * fs_ld : SC + (int64_t)b * k * kRowBlock, FS != nullptr, n_valid, sh,
-                      out_s + (int64_t)b * k, out_i + (int64_t)b * k);
+    out_s += (int64_t)b * k;
+    out_i += (int64_t)b * k;
+    if (FS)
+        final_select<VPT, true>(first_row, k, FS + b * fs_ld, n_valid, sh, out_s, out_i);
+    else
+        final_select<VPT, false>(first_row, k, SC + (int64_t)b * k * kRowBlock, n_valid, sh, out_s, out_i);
 }
 
 // Steps 1 and 3 in one launch, for scans that wrote every score: one workgroup
@@ -246,11 +271,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_scored_kernel(const uint64_t
     {
         const uint64_t* row = G + (int64_t)b * g_ld;
         uint64_t v[VPT];
-#pragma unroll
-        for (int j = 0; j < VPT; j++) {
-            const int64_t at = j * kSelThreads + t;
-            v[j] = at < n_rb ? row[at] : 0ull;
-        }
+        load_keys(v, row, 0, n_rb);
         block_select(v, k, sh);
     }
     if (t < k) {
@@ -258,7 +279,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_scored_kernel(const uint64_t
         first_row[t] = bk ? (int64_t)(key_pos(bk) / kRowBlock) * kRowBlock : -1;
     }
     __syncthreads();
-    final_select<FVPT>(first_row, k, FS + b * fs_ld, true, n_valid, sh, out_s + (int64_t)b * k, out_i + (int64_t)b * k);
+    final_select<FVPT, true>(first_row, k, FS + b * fs_ld, n_valid, sh, out_s + (int64_t)b * k, out_i + (int64_t)b * k);
 }
 
 int64_t topk_chunks(int64_t n) { return n <= 0 ? 1 : (n + kBlkSpan - 1) / kBlkSpan; }
