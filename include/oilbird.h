@@ -154,7 +154,11 @@ int32_t oil_pool_append(oil_pool *pool, const void *keys, int32_t key_dtype, con
 
 /* Workspace bytes oil_pool_query_topk needs for B queries and k neighbours
  * (sized from the pool's capacity, so it stays valid as the pool grows; with
- * bf16 keys and B <= 4 it includes room for up to 2 MiB of scores). */
+ * bf16 keys and B <= 4 it includes room for up to 2 MiB of scores, otherwise,
+ * while the pool is small enough for the scan to write every score, room for
+ * those: up to 16 MiB for B <= 64, 512 MiB above.  A workspace without that
+ * room, sized when the pool was larger, serves too: the chosen blocks are then
+ * scored again, with the same results). */
 size_t oil_query_workspace_bytes(const oil_pool *pool, int32_t B, int32_t k);
 
 /* Retrieval (Algorithm 1 retrieve step, Eq. 2): normalise each query row as
@@ -183,8 +187,8 @@ int32_t oil_pool_query_topk(const oil_pool *pool, const void *queries, int32_t q
  * workspace is a static device array inside the library, one copy per GPU,
  * OIL_QUERY_SCRATCH_BYTES long, held by each GPU the library runs on until
  * the process ends.  A request whose workspace
- * (oil_query_workspace_bytes(pool, B, k), sized from the pool's capacity)
- * exceeds it returns OIL_E_SCRATCH and enqueues nothing; 32 MiB covers, e.g.,
+ * (oil_query_workspace_bytes(pool, B, k), sized from the pool's capacity,
+ * without the room for every score past B = 4) exceeds it returns OIL_E_SCRATCH and enqueues nothing; 32 MiB covers, e.g.,
  * B = 64 queries with k = 32 over a pool of 1,048,576 positions of width 4096.
  * `stream` must belong to the current device (else OIL_E_INVALID).  No device
  * memory is allocated or freed and nothing needs to start at zero.  Calls on

@@ -73,9 +73,12 @@ QueryWorkspace carve(const oil_pool* p, int32_t B, int32_t k, bool full = true)
     // rescored: the GEMV scan (bf16, B <= 4) while B * n_valid <=
     // kGemvScoresMax, the MFMA scan up to scan_full_rows positions
     const bool gemv = p->fmt != oil::kKeyFp8 && !oil::scan_uses_mfma(B, p->ld);
-    const int64_t fs_max = gemv ? (oil::kGemvScoresMax / B) / 64 * 64 : oil::scan_full_rows(B, k, (int64_t)p->ld * (p->fmt == oil::kKeyFp8 ? 1 : 2));
+    const int64_t row_bytes = (int64_t)p->ld * (p->fmt == oil::kKeyFp8 ? 1 : 2);
+    const int64_t fs_max =
+        gemv ? (oil::kGemvScoresMax / B) / 64 * 64 : oil::scan_full_rows(B, k, row_bytes);
     // (a pool past them never comes back: it needs no room)
-    w.fs_ld = gemv || (full && p->n_valid <= fs_max) ? std::min((int64_t)round_up((size_t)p->capacity, 64), fs_max) : 0;
+    const bool room = gemv || (full && p->n_valid <= fs_max);
+    w.fs_ld = room ? std::min((int64_t)round_up((size_t)p->capacity, 64), fs_max) : 0;
     const size_t fs_bytes = (size_t)B * (size_t)w.fs_ld * sizeof(float);
     w.q_off = 0;
     w.sc_off = round_up(w.q_off + q_bytes, kAlign);
@@ -408,7 +411,9 @@ int32_t oil_pool_query_topk(const oil_pool* pool, const void* queries, int32_t q
     const int32_t st = query_args_status(pool, queries, q_dtype, B, k, exclude_prompt, scores, idx);
     if (st != OIL_OK)
         return st;
-    const QueryWorkspace w = carve(pool, B, k);
+    QueryWorkspace w = carve(pool, B, k);
+    if (workspace_bytes < w.total)  // sized for a fuller pool over the same buffers, say
+        w = carve(pool, B, k, false);
     if (!workspace || workspace_bytes < w.total || !aligned(workspace, kAlign))
         return OIL_E_WORKSPACE;
     return query_topk_enqueue(pool, queries, q_dtype, B, k, exclude_prompt, (char*)workspace, w, scores, idx,

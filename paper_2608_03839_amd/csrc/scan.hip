@@ -1503,13 +1503,13 @@ static void launch_wide(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws
 //    512 queries 262 / 391 / 804 against 225 / 289 / 551; 400,001 positions
 //    663 / 975 / 1,804 against 692 / 894 / 1,692; 800,000 positions 1,216 /
 //    1,777 / 3,254 against 1,449 / 1,749 / 3,402; fp8 keys, 400,001 positions
-//    390 / 600 / 1,087 against 416 / 592 / 1,056.  At most 1 GiB.
+//    390 / 600 / 1,087 against 416 / 592 / 1,056.  At most 512 MiB.
 int64_t scan_full_rows(int32_t B, int32_t k, int64_t row_bytes)
 {
     if (B <= 64)
         return 2048 * kRowBlock;
     const int64_t even = (int64_t)k * kRowBlock * row_bytes / (B <= 128 ? 14 : 5);
-    return std::max<int64_t>(1024 * kRowBlock, std::min<int64_t>(even, (1 << 28) / B) / 64 * 64);
+    return std::max<int64_t>(1024 * kRowBlock, std::min<int64_t>(even, (1 << 27) / B) / 64 * 64);
 }
 
 hipError_t launch_scan(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,

@@ -115,3 +115,28 @@ def test_noalloc_rejects_requests_beyond_the_scratch(oil):
                                        None)
     assert st == -6
     assert L.oil_pool_destroy(h) == 0
+
+
+def test_workspace_of_a_full_pool_serves_a_new_one(oil):
+    """A workspace sized while a pool was past the sizes whose scan writes every
+    score serves a new handle over the same buffers (few positions, room for
+    full scores wanted but not needed), with the same results."""
+    wp, pool = _pool(oil, 70000, 64, seed=91)
+    q, _ = workloads.queries(wp, workloads.QuerySpec(B=8, p_random=0.25, seed=92))
+    q = q.float().cuda()
+    small = torch.empty(oil.query_workspace_bytes(pool.handle, 8, 16), dtype=torch.uint8, device="cuda")
+    h = oil.pool_create(64, 70000, pool.keys, pool.tokens, pool.traces, pool.prompts)
+    raw = wp.raw_rows(0, 3000).cuda()
+    ids = [t[:3000].cuda() for t in (wp.tokens, wp.traces, wp.prompts)]
+    oil.pool_append(h, raw, *ids)
+    assert oil.query_workspace_bytes(h, 8, 16) > small.numel()
+    large = torch.empty(oil.query_workspace_bytes(h, 8, 16), dtype=torch.uint8, device="cuda")
+    out = []
+    for ws in (small, large):
+        s, i = torch.empty(8, 16, device="cuda"), torch.empty(8, 16, dtype=torch.int32, device="cuda")
+        oil.pool_query_topk(h, q, 16, ws, s, i)
+        out.append((s, i))
+    torch.cuda.synchronize()
+    oil.pool_destroy(h)
+    assert torch.equal(out[0][1], out[1][1])
+    assert torch.equal(out[0][0].view(torch.int32), out[1][0].view(torch.int32))
