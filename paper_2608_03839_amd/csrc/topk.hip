@@ -6,7 +6,8 @@
 // low word; 0 = "no position").  Keys are distinct, so "the k largest keys"
 // is exact and independent of evaluation order.
 //
-// The scan leaves the largest key of each 32-row block ("block key").  The k
+// The scan leaves a word per 32-row block (block_word) that, with the block's
+// number, makes the block's largest key ("block key").  The k
 // largest keys of the pool lie inside the k row blocks with the largest
 // block keys: if a top-k key's block were not among them, those k blocks
 // would hold k keys above it.  So:
@@ -15,8 +16,9 @@
 //      until one list of k remains; up to 4096 block keys, one workgroup
 //      takes them all);
 //   2. the rescore kernel (scan.hip) recomputes the 32 scores of each chosen
-//      block, bit-identical to the scan's (for the GEMV scan's batches, which
-//      write every score, the final step reads them instead);
+//      block that can hold a second hit, bit-identical to the scan's (a scan that
+//      wrote every score needs none: the final step reads them, and up to 4096
+//      block keys steps 1 and 3 are one launch);
 //   3. select the k largest of those k * 32 keys, ranked and written in order.
 // Selection inside a workgroup is a radix select over 8-bit digits of the
 // 64-bit keys (LDS histogram with wave-aggregated increments; it stops as
