@@ -211,7 +211,8 @@ __global__ __launch_bounds__(256) void recycle_keys_kernel(
             for (int j = 1; j < NI; j++)
                 y[p] = j == i ? x[j][p] : y[p];
         }
-        dst[i * 64 + lane] = settle_chunk_bf16<F32>(y, sc);
+        bool divided;
+        dst[i * 64 + lane] = settle_chunk_bf16<F32>(y, sc, divided);
     }
 }
 

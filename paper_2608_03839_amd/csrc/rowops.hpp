@@ -115,22 +115,70 @@ __device__ __forceinline__ bool bf16_near(float q)
 }
 
 // The bf16 value that v / norm rounds to, for q = v * inv with bf16_near(q).
-__device__ __forceinline__ uint16_t bf16_settle(float v, float q, const RowScale& s)
+// divided: set where the last bits of s.norm decide.
+__device__ __forceinline__ uint16_t bf16_settle(float v, float q, const RowScale& s, bool& divided)
 {
     const uint32_t u = __float_as_uint(q);
     const float mid = __uint_as_float((u & 0xFFFF0000u) | 0x8000u);
     const float above = (q - mid) + quotient_rest(v, q, s);  // q - mid is a few ulps: exact
-    if (!s.fast || (u << 1) - 1u < (54u << 24) || !(fabsf(above) > fabsf(q) * 0x1p-40f))
+    if (!s.fast || (u << 1) - 1u < (54u << 24) || !(fabsf(above) > fabsf(q) * 0x1p-40f)) {
+        divided = true;
         return double_to_bf16_rne((double)v / s.norm);
+    }
     return (uint16_t)((u >> 16) + ((above > 0.f) != (q < 0.f) ? 1u : 0u));
 }
 
-__device__ __forceinline__ uint16_t unit_bf16(float v, const RowScale& s)
+__device__ __forceinline__ uint16_t unit_bf16(float v, const RowScale& s, bool& divided)
 {
     const float q = v * s.inv;
     if (!s.fast || bf16_near(q))
-        return bf16_settle(v, q, s);
+        return bf16_settle(v, q, s, divided);
     return (uint16_t)((__float_as_uint(q) + 0x8000u) >> 16);
+}
+
+// The norm of the raw row that starts at element `at`, by one wave (all lanes,
+// the same row), with the additions of normalize_row<NT>: the same bits.  Kernels
+// whose lanes hold whole chunks of a row sum its squares in another order.  That
+// norm is within 2^-46 of this one, which leaves every value as it is that the
+// residual settles (it stays 2^-40 away from the middle); only for the values
+// that are divided, none at all in ordinary rows, do they need this one.
+template <int NT, bool F32>
+__device__ __attribute__((noinline)) double column_order_norm(const void* __restrict__ raw, int64_t at, int32_t d)
+{
+    double sum = 0.0;
+#pragma unroll 1
+    for (int w = 0; w < NT / 64; w++) {
+        double ss = 0.0;
+#pragma unroll 1
+        for (int32_t j = w * 64 + (int)(threadIdx.x & 63); j < d; j += NT) {
+            const double x = load_raw(raw, F32 ? 0 : 1, at + j);
+            ss += x * x;
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1)
+            ss += __shfl_xor(ss, o, kWave);
+        sum += ss;
+    }
+    return sqrt(sum);
+}
+
+// Gives the lanes that need it that norm of their row: lane l of a wave has row
+// l % R, which starts at element `at`.  Every lane of the wave takes part.
+template <int NT, bool F32, int R>
+__device__ __forceinline__ void column_order_norms(bool need, const void* __restrict__ raw, int64_t at, int32_t d,
+                                                   double& norm)
+{
+    constexpr uint64_t kRow0 = R == 1 ? ~0ull : R == 4 ? 0x1111111111111111ull : 0x0101010101010101ull;
+    static_assert(R == 1 || R == 4 || R == 8, "rows per wave");
+    const uint64_t wanted = __ballot(need);
+#pragma unroll 1
+    for (int r = 0; r < R; r++) {
+        if (!(wanted & (kRow0 << r)))
+            continue;
+        const double exact = column_order_norm<NT, F32>(raw, __shfl(at, r, kWave), d);
+        if ((int)(threadIdx.x & (R - 1)) == r)
+            norm = exact;
+    }
 }
 
 // Eight columns c .. c + 7 of the raw row that starts at element `at` (d
@@ -195,7 +243,7 @@ __device__ __forceinline__ u32x4 unit_chunk_bf16(const u32x4 (&x)[F32 ? 2 : 1], 
 
 // The same with every value settled (zeros for a zero or NaN row).
 template <bool F32>
-__device__ __forceinline__ u32x4 settle_chunk_bf16(const u32x4 (&x)[F32 ? 2 : 1], const RowScale& sc)
+__device__ __forceinline__ u32x4 settle_chunk_bf16(const u32x4 (&x)[F32 ? 2 : 1], const RowScale& sc, bool& divided)
 {
     u32x4 w = {0, 0, 0, 0};
     if (!(sc.norm > 0.0))
@@ -205,7 +253,7 @@ __device__ __forceinline__ u32x4 settle_chunk_bf16(const u32x4 (&x)[F32 ? 2 : 1]
 #pragma unroll
         for (int f = 0; f < 8; f++)
             v = f == e ? chunk_value<F32>(x, f) : v;
-        const uint32_t bits = (uint32_t)unit_bf16(v, sc) << ((e & 1) * 16);
+        const uint32_t bits = (uint32_t)unit_bf16(v, sc, divided) << ((e & 1) * 16);
 #pragma unroll
         for (int q = 0; q < 4; q++)
             w[q] |= q == (e >> 1) ? bits : 0u;
@@ -222,11 +270,12 @@ __device__ __forceinline__ void normalize_row_regs(const void* raw, int dtype, i
     float v[NV];
     load_row<NT, NV>(raw, dtype, row, d, live, v);
     const RowScale sc = row_scale(sqrt(block_sum<NT>(sum_squares(v), red)));
+    bool divided;
 #pragma unroll
     for (int i = 0; i < NV; i++) {
         const int32_t j = i * NT + t;
         if (j < ld)
-            dst(j, (j < d && sc.norm > 0.0) ? unit_bf16(v[i], sc) : (uint16_t)0);
+            dst(j, (j < d && sc.norm > 0.0) ? unit_bf16(v[i], sc, divided) : (uint16_t)0);
     }
 }
 

@@ -9,7 +9,9 @@
 // appends: store_rows_kernel, eight rows per workgroup.  The squared norm is
 // accumulated in double, each quotient by it rounded once (RowScale: nearly
 // all of them without a division), so identical raw rows always produce
-// identical stored bits wherever they sit in the pool.
+// identical stored bits, wherever they sit in the pool and whichever of the
+// kernels took them: where the last bits of the norm decide a value, the bulk
+// kernel sums the squares again in the one-row kernels' order.
 #include <type_traits>
 
 #include "common.hpp"
@@ -105,16 +107,18 @@ __device__ __forceinline__ bool e4m3_near(float q)
 
 // The code that the scaled quotient v / norm * 2^shift rounds to, for q =
 // v * s.inv with s already scaled by 2^shift (its norm is not) and a near
-// number of steps.
-__device__ __forceinline__ uint8_t e4m3_settle(float v, float q, const RowScale& s, int shift)
+// number of steps.  divided: set where the last bits of s.norm decide.
+__device__ __forceinline__ uint8_t e4m3_settle(float v, float q, const RowScale& s, int shift, bool& divided)
 {
     float scale;
     int base;
     const float a = e4m3_steps(q, scale, base), low = floorf(a);
     const float rest = quotient_rest(v, q, s) * scale;
     const float above = (a - (low + 0.5f)) + (q < 0.f ? -rest : rest);
-    if (!s.fast || !(fabsf(above) > a * 0x1p-40f))
+    if (!s.fast || !(fabsf(above) > a * 0x1p-40f)) {
+        divided = true;
         return double_to_e4m3_rne(ldexp((double)v / s.norm, shift));
+    }
     return (uint8_t)(((__float_as_uint(q) >> 24) & 0x80u) |
                      (uint32_t)(base + (int)low + (above > 0.f ? 1 : 0)));
 }
@@ -127,11 +131,11 @@ __device__ __forceinline__ RowScale scaled(RowScale s, int shift)
     return s;
 }
 
-__device__ __forceinline__ uint8_t unit_e4m3(float v, const RowScale& s, int shift)
+__device__ __forceinline__ uint8_t unit_e4m3(float v, const RowScale& s, int shift, bool& divided)
 {
     const float q = v * s.inv;
     if (!s.fast || e4m3_near(q))
-        return e4m3_settle(v, q, s, shift);
+        return e4m3_settle(v, q, s, shift, divided);
     return (uint8_t)__builtin_amdgcn_cvt_pk_fp8_f32(q, q, 0, false);
 }
 
@@ -171,6 +175,12 @@ __device__ __forceinline__ double block_max(double m, double* red)
 // Power-of-two scale shift putting the row's largest magnitude m in [128, 256).
 __device__ __forceinline__ int fp8_shift(double m) { return m > 0.0 ? 7 - ilogb(m) : 0; }
 
+// Whether m is so near a power of two that the last bits of the norm decide it.
+__device__ __forceinline__ bool fp8_shift_near(double m)
+{
+    return fp8_shift(m * (1.0 + 0x1p-40)) != fp8_shift(m * (1.0 - 0x1p-40));
+}
+
 // One row of quantize_rows_kernel for ld8 <= NT * NV, read once into
 // registers; the same arithmetic as the general path.  Returns the shift.
 template <int NT, int NV, class Dst>
@@ -188,11 +198,12 @@ __device__ __forceinline__ int quantize_row_regs(const void* raw, int dtype, int
         top = fmaxf(top, fabsf(v[i]));
     const int shift = fp8_shift(block_max<NT>(sc.norm > 0.0 ? (double)top / sc.norm : 0.0, red));
     const RowScale s8 = scaled(sc, shift);
+    bool divided;
 #pragma unroll
     for (int i = 0; i < NV; i++) {
         const int32_t j = i * NT + t;
         if (j < ld8)
-            dst(j, (j < d && sc.norm > 0.0) ? unit_e4m3(v[i], s8, shift) : (uint8_t)0);
+            dst(j, (j < d && sc.norm > 0.0) ? unit_e4m3(v[i], s8, shift, divided) : (uint8_t)0);
     }
     return shift;
 }
@@ -289,7 +300,8 @@ __device__ __forceinline__ u32x4 unit_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1], 
 
 // The same with every value settled (zeros for a zero or NaN row).
 template <bool F32>
-__device__ __forceinline__ u32x4 settle_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1], const RowScale& s, int shift)
+__device__ __forceinline__ u32x4 settle_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1], const RowScale& s, int shift,
+                                                bool& divided)
 {
     u32x4 w = {0, 0, 0, 0};
     if (!(s.norm > 0.0))
@@ -299,7 +311,7 @@ __device__ __forceinline__ u32x4 settle_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1]
 #pragma unroll
         for (int f = 0; f < 16; f++)
             v = f == e ? chunk_value<F32>(x[f >> 3], f & 7) : v;
-        const uint32_t bits = (uint32_t)unit_e4m3(v, s, shift) << ((e & 3) * 8);
+        const uint32_t bits = (uint32_t)unit_e4m3(v, s, shift, divided) << ((e & 3) * 8);
 #pragma unroll
         for (int q = 0; q < 4; q++)
             w[q] |= q == (e >> 2) ? bits : 0u;
@@ -307,8 +319,16 @@ __device__ __forceinline__ u32x4 settle_e4m3_16(const u32x4 (&x)[2][F32 ? 2 : 1]
     return w;
 }
 
+// Wavefronts per SIMD that the registers must leave room for: three workgroups
+// per compute unit where a thread's raw values fit 40 registers, else two.
+constexpr int bulk_waves(int fmt, bool f32, bool vec, int ni)
+{
+    return vec && ni * (fmt == kKeyFp8 ? 2 : 1) * (f32 ? 8 : 4) <= 40 ? 6 : 4;
+}
+
 template <int FMT, bool F32, bool VEC, int NI, int R>
-__global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4))) void store_rows_kernel(
+__global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(bulk_waves(FMT, F32, VEC, NI)))) void
+store_rows_kernel(
     const void* __restrict__ raw, int32_t d, int64_t n, uint8_t* __restrict__ out, int64_t row_offset, int32_t ld,
     int64_t rs, int64_t ws, float* __restrict__ inv_scale, const int32_t* __restrict__ tok_in,
     const int32_t* __restrict__ trace_in, const int32_t* __restrict__ prompt_in, int32_t* __restrict__ tok_out,
@@ -373,8 +393,6 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4)
         if constexpr (FMT == kKeyFp8)
             top = fmaxf(top, redm[w][r]);
     }
-    if (!live)
-        return;
     if constexpr (!F32) {
         // unpacked again below: the floats of the norm would otherwise stay in
         // registers beside the raw pieces (half the workgroups in flight)
@@ -387,7 +405,11 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4)
     RowScale sc = row_scale(sqrt(ss));
     int shift = 0;
     if constexpr (FMT == kKeyFp8) {
-        shift = fp8_shift(sc.norm > 0.0 ? (double)top / sc.norm : 0.0);
+        const auto largest = [&] { return sc.norm > 0.0 ? (double)top / sc.norm : 0.0; };
+        const bool near = live && fp8_shift_near(largest());
+        if (__any(near))
+            column_order_norms<kRowThreads, F32, R>(near, raw, at, d, sc.norm);
+        shift = fp8_shift(largest());
         sc = scaled(sc, shift);
     }
     uint8_t* base = out + (dst >> 5) * rs;
@@ -403,7 +425,7 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4)
     uint32_t open = 0;
 #pragma unroll
     for (int i = 0; i < NI; i++) {
-        if (u0 + i * kUnits >= units)
+        if (!live || u0 + i * kUnits >= units)
             break;
         bool near;
         u32x4 w;
@@ -414,6 +436,15 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4)
         put(i, w);
         open |= near ? 1u << i : 0u;
     }
+    auto settle = [&](int i, const u32x4(&y)[H][F32 ? 2 : 1]) -> bool {
+        bool divided = false;
+        if constexpr (FMT == kKeyFp8)
+            put(i, settle_e4m3_16<F32>(y, sc, shift, divided));
+        else
+            put(i, settle_chunk_bf16<F32>(y[0], sc, divided));
+        return divided;
+    };
+    uint32_t divided = 0;  // units with a value that the norm's last bits decide
     while (open) {
         const int i = __ffs((int)open) - 1;
         open &= open - 1;
@@ -427,12 +458,27 @@ __global__ __launch_bounds__(kBulkThreads) __attribute__((amdgpu_waves_per_eu(4)
                 for (int j = 1; j < NI; j++)
                     y[h][p] = j == i ? x[j][h][p] : y[h][p];
             }
-        if constexpr (FMT == kKeyFp8)
-            put(i, settle_e4m3_16<F32>(y, sc, shift));
-        else
-            put(i, settle_chunk_bf16<F32>(y[0], sc));
+        divided |= settle(i, y) ? 1u << i : 0u;
     }
-    if (u0 == 0) {  // one lane per row
+    if (__any(divided)) {
+        // (the row's place is worked out again, and the row read again, so that
+        // no register holds them until here)
+        int64_t first = row_offset;
+        asm volatile("" : "+s"(first));
+        const int64_t src2 = (first / R + blockIdx.x) * R + r - first;
+        const int64_t at2 = (src2 >= 0 && src2 < n ? src2 : 0) * d;
+        column_order_norms<kRowThreads, F32, R>(divided != 0, raw, at2, d, sc.norm);
+        while (divided) {
+            const int i = __ffs((int)divided) - 1;
+            divided &= divided - 1;
+            u32x4 y[H][F32 ? 2 : 1];
+#pragma unroll
+            for (int h = 0; h < H; h++)
+                load_chunk<F32, VEC>(raw, at2, col_of(u0 + i * kUnits, h), d, y[h]);
+            settle(i, y);
+        }
+    }
+    if (live && u0 == 0) {  // one lane per row
         if constexpr (FMT == kKeyFp8)
             inv_scale[dst] = ldexpf(1.f, -shift);
         tok_out[dst] = tok_in[src];

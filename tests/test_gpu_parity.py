@@ -124,12 +124,63 @@ def test_bulk_append_matches_oracle(oil, key_format, n, d, dtype):
         diff = np.abs(got.astype(np.int32) - ref.astype(np.int32))
         assert np.array_equal(pool.scales.cpu().numpy()[:n + 13].astype(np.float64), inv)
         past = untile_keys_fp8(pool.keys.cpu().numpy(), n + 50, pool.stride, pool.capacity)
-    # the norm's sum may round differently in its last bit: at most one step, hardly ever
+    # the oracle adds the squares in another order, so a norm may differ in its last
+    # bit: at most one step, hardly ever
     assert diff.max() <= 1 and (diff > 0).mean() <= 1e-6
     assert np.array_equal(got[20:28], ref[20:28])
     assert np.all(past[:, d:] == 0) and np.all(past[n + 13:] == 0)
     for t, off in ((pool.tokens, 0), (pool.traces, 1), (pool.prompts, 2)):
         assert torch.equal(t[:n + 13].cpu(), ids + off)
+
+
+def _order_rows(n, d, dtype, seed):
+    """Rows whose sum of squares is 2^60 or a unit or two above it by the order of
+    its additions (large values whose squares add up to 2^60 exactly, among small
+    ones of which some are lost), with a quotient that is halfway between two
+    stored values for the one norm (up, to the even one) and below that for
+    the other."""
+    rng = np.random.default_rng(seed)
+    if dtype == "f32":   # 259 / 512: halfway between bf16 values; 304 / 512 = 19 / 32: between E4M3 ones
+        large = np.array([259, 304, *_four_squares(512 * 512 - 259 * 259 - 304 * 304)], np.float32) * 2.0 ** 21
+    else:
+        large = np.array([25, 19, 6, 1, 1], np.float32) * 2.0 ** 25
+    raw = np.zeros((n, d), np.float32)
+    for row in raw:
+        # near one another, in lanes that meet early, or anywhere
+        span = min(d, int(rng.choice([16, 64, 512, 2048, d])))
+        at = rng.integers(0, d - span + 1) + rng.choice(span, size=min(span, len(large) + 10), replace=False)
+        row[at[:len(large)]] = large
+        small = at[len(large):]
+        row[small] = rng.choice([5.5, 6.5, 7.75, 9.0, 11.0], len(small))
+    raw[::2] *= 2.0 ** rng.integers(-40, 5, (len(raw[::2]), 1))
+    return torch.from_numpy(raw).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+
+
+@pytest.mark.parametrize("key_format", ["bf16", "fp8"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [100, 512, 1100, 2048, 4001, 4096, 5001, 5120, 6144, 8190, 8192])
+def test_bulk_append_stores_the_same_bits(oil, key_format, dtype, d):
+    """A row's stored bits do not depend on the call that brought it: a bulk
+    append gives those of appends too small for the bulk kernel, for rows whose
+    norm depends on the order of its sum."""
+    n = 700
+    raw = _order_rows(n, d, dtype, seed=d)
+    raw[1::7] = torch.randn((len(raw[1::7]), d), generator=torch.Generator().manual_seed(d)).to(raw.dtype)
+    raw = raw.cuda()
+    ids = torch.arange(n, dtype=torch.int32).cuda()
+    pools = []
+    for step in (n, 350):
+        pool = oil.Pool(d, n, key_format=key_format)
+        pool.keys.zero_()
+        for s in range(0, n, step):
+            pool.append(raw[s:s + step].clone(), ids[s:s + step], ids[s:s + step], ids[s:s + step])
+        pools.append(pool)
+    torch.cuda.synchronize()
+    a, b = pools
+    wide = torch.int16 if key_format == "bf16" else torch.uint8
+    assert torch.equal(a.keys.view(wide), b.keys.view(wide))
+    if key_format == "fp8":
+        assert torch.equal(a.scales, b.scales)
 
 
 # ---------------------------------------------------------------- retrieval (Eq. 2)
