@@ -147,6 +147,8 @@ __global__ __launch_bounds__(256) void recycle_plan_kernel(
     rec_slot[k] = (int32_t)slot;
 }
 
+constexpr int kWideThreads = 256;
+
 // One wave per record: lane l takes the 8-column chunks l, l + 64, ... of the
 // row (NI of them hold it), which stays in registers between its norm and the
 // rounding.  VEC: whole 16-byte pieces of every row are aligned.  1,260
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(256) void recycle_keys_kernel(
         for (int i = 0; i < NI; i++)
             asm volatile("" : "+v"(x[i][0]));
     }
-    const RowScale sc = row_scale(sqrt(ss));
+    RowScale sc = row_scale(sqrt(ss));
     uint32_t open = 0;
 #pragma unroll
     for (int i = 0; i < NI; i++) {
@@ -200,6 +202,7 @@ __global__ __launch_bounds__(256) void recycle_keys_kernel(
             open |= near ? 1u << i : 0u;
         }
     }
+    uint32_t divided = 0;  // chunks with a value that the norm's last bits decide
     while (open) {  // the few chunks with a value not decided: settled and stored again
         const int i = __ffs((int)open) - 1;
         open &= open - 1;
@@ -211,18 +214,31 @@ __global__ __launch_bounds__(256) void recycle_keys_kernel(
             for (int j = 1; j < NI; j++)
                 y[p] = j == i ? x[j][p] : y[p];
         }
-        bool divided;
-        dst[i * 64 + lane] = settle_chunk_bf16<F32>(y, sc, divided);
+        bool div = false;
+        dst[i * 64 + lane] = settle_chunk_bf16<F32>(y, sc, div);
+        divided |= div ? 1u << i : 0u;
+    }
+    if (__any(divided)) {
+        column_order_norms<kWideThreads, F32, 1>(divided != 0, states, at, d, sc.norm);
+        while (divided) {  // read again, so that no register holds the row until here
+            const int i = __ffs((int)divided) - 1;
+            divided &= divided - 1;
+            u32x4 y[F32 ? 2 : 1];
+            load_chunk<F32, VEC>(states, at, (i * 64 + lane) * 8, d, y);
+            bool div;
+            dst[i * 64 + lane] = settle_chunk_bf16<F32>(y, sc, div);
+        }
     }
 }
 
-// The same for rows wider than 8,192 columns: one 256-thread block per record.
-__global__ __launch_bounds__(256) void recycle_wide_keys_kernel(
+// The same for rows wider than 8,192 columns: one block per record.  Its order of
+// additions defines the norm of a record's key at every width.
+__global__ __launch_bounds__(kWideThreads) void recycle_wide_keys_kernel(
     const void* __restrict__ states, int dtype, int32_t d, int32_t ld, const int32_t* __restrict__ rec_src,
     const int32_t* __restrict__ rec_slot, const int64_t* __restrict__ total_in, int64_t capacity,
     uint16_t* __restrict__ keys, int64_t* __restrict__ head)
 {
-    __shared__ double red[4];
+    __shared__ double red[kWideThreads / 64];
     const int64_t total = *total_in;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         *head += total;  // no kernel of this call reads the head after the plan
@@ -230,7 +246,8 @@ __global__ __launch_bounds__(256) void recycle_wide_keys_kernel(
     for (int64_t k = first + blockIdx.x; k < total; k += gridDim.x) {
         const int64_t row = rec_src[k];
         uint16_t* dst = keys + (int64_t)rec_slot[k] * ld;
-        normalize_row<256>(states, dtype, row, d, ld, true, red, [&](int32_t j, uint16_t bits) { dst[j] = bits; });
+        normalize_row<kWideThreads>(states, dtype, row, d, ld, true, red,
+                                    [&](int32_t j, uint16_t bits) { dst[j] = bits; });
     }
 }
 
@@ -471,7 +488,7 @@ hipError_t launch_recycle_insert(int32_t B, int32_t max_nodes, const int32_t* no
     const int64_t most = (int64_t)B * (max_nodes - 1);
     if (ld > 8192) {
         const int grid = (int)(most < 1 ? 1 : (most < 2048 ? most : 2048));
-        hipLaunchKernelGGL(recycle_wide_keys_kernel, dim3(grid), dim3(256), 0, stream, states, dtype, d, ld, rec_src,
+        hipLaunchKernelGGL(recycle_wide_keys_kernel, dim3(grid), dim3(kWideThreads), 0, stream, states, dtype, d, ld, rec_src,
                            rec_slot, total, capacity, keys, head);
         return hipGetLastError();
     }

@@ -66,6 +66,40 @@ def untile_keys_fp8(buf, n, dim, capacity):
     return np.ascontiguousarray(rows[:n, :dim])
 
 
+def four_squares(m):
+    """a, b, c, e with a^2 + b^2 + c^2 + e^2 = m."""
+    for e in range(4):
+        for a in range(int((m - e * e) ** 0.5), 0, -1):
+            for b in range(int((m - e * e - a * a) ** 0.5), -1, -1):
+                c = int(round((m - e * e - a * a - b * b) ** 0.5))
+                if a * a + b * b + c * c + e * e == m:
+                    return a, b, c, e
+    raise ValueError(m)
+
+
+def order_rows(n, d, dtype, seed):
+    """Rows (float32, exact in bf16 too unless dtype is "f32") whose sum of squares
+    is 2^60 or a unit or two above it by the order of its additions (large values
+    whose squares add up to 2^60 exactly, among small ones of which some are
+    lost), with a quotient that is halfway between two stored values for the one
+    norm (up, to the even one) and below that for the other."""
+    rng = np.random.default_rng(seed)
+    if dtype == "f32":   # 259 / 512: halfway between bf16 values; 304 / 512 = 19 / 32: between E4M3 ones
+        large = np.array([259, 304, *four_squares(512 * 512 - 259 * 259 - 304 * 304)], np.float32) * 2.0 ** 21
+    else:
+        large = np.array([25, 19, 6, 1, 1], np.float32) * 2.0 ** 25
+    raw = np.zeros((n, d), np.float32)
+    for row in raw:
+        # near one another, in lanes that meet early, or anywhere
+        span = min(d, int(rng.choice([16, 64, 512, 2048, d])))
+        at = rng.integers(0, d - span + 1) + rng.choice(span, size=min(span, len(large) + 10), replace=False)
+        row[at[:len(large)]] = large
+        small = at[len(large):]
+        row[small] = rng.choice([5.5, 6.5, 7.75, 9.0, 11.0], len(small))
+    raw[::2] *= 2.0 ** rng.integers(-40, 5, (len(raw[::2]), 1))
+    return raw
+
+
 def oracle_rows(keys_bits, raw_q, prompt=None, exclude=None):
     """Oracle scores of every position (excluded -> -inf) for each raw query."""
     q = oracle.normalize_rows(raw_q)

@@ -11,8 +11,8 @@ import torch
 
 import oracle
 import workloads
-from tests._parity import (TOL, away_from_edges, check_topk, fp32_bound, oracle_rows, untile_keys,
-                           untile_keys_fp8)
+from tests._parity import (TOL, away_from_edges, check_topk, four_squares, fp32_bound, oracle_rows,
+                           order_rows, untile_keys, untile_keys_fp8)
 
 pytestmark = pytest.mark.gpu
 
@@ -76,17 +76,6 @@ def test_store_matches_oracle(oil, d, dtype):
     assert torch.equal(pool.prompts[:n].cpu(), wp.prompts)
 
 
-def _four_squares(m):
-    """a, b, c, e with a^2 + b^2 + c^2 + e^2 = m."""
-    for e in range(4):
-        for a in range(int((m - e * e) ** 0.5), 0, -1):
-            for b in range(int((m - e * e - a * a) ** 0.5), -1, -1):
-                c = int(round((m - e * e - a * a - b * b) ** 0.5))
-                if a * a + b * b + c * c + e * e == m:
-                    return a, b, c, e
-    raise ValueError(m)
-
-
 @pytest.mark.parametrize("key_format", ["bf16", "fp8"])
 @pytest.mark.parametrize("n,d,dtype", [(639, 4096, "bf16"), (640, 4096, "bf16"), (777, 512, "f32"), (700, 1100, "f32"),
                                        (701, 4001, "bf16"), (650, 5001, "f32"), (641, 2880, "bf16"), (655, 5120, "f32"),
@@ -105,7 +94,7 @@ def test_bulk_append_matches_oracle(oil, key_format, n, d, dtype):
     raw[24:28] = 0
     for j, odd in enumerate((257, 259, 265, 273)):
         # norm 512: odd / 512 lies halfway between bf16 values, 272 / 512 = 17 / 32 between E4M3 ones
-        rest = _four_squares(512 * 512 - odd * odd - 272 * 272)
+        rest = four_squares(512 * 512 - odd * odd - 272 * 272)
         raw[24 + j, :6] = torch.tensor([odd, -272, *rest], dtype=torch.float32)
     raw = raw.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
     ids = torch.arange(n + 13, dtype=torch.int32)
@@ -133,29 +122,6 @@ def test_bulk_append_matches_oracle(oil, key_format, n, d, dtype):
         assert torch.equal(t[:n + 13].cpu(), ids + off)
 
 
-def _order_rows(n, d, dtype, seed):
-    """Rows whose sum of squares is 2^60 or a unit or two above it by the order of
-    its additions (large values whose squares add up to 2^60 exactly, among small
-    ones of which some are lost), with a quotient that is halfway between two
-    stored values for the one norm (up, to the even one) and below that for
-    the other."""
-    rng = np.random.default_rng(seed)
-    if dtype == "f32":   # 259 / 512: halfway between bf16 values; 304 / 512 = 19 / 32: between E4M3 ones
-        large = np.array([259, 304, *_four_squares(512 * 512 - 259 * 259 - 304 * 304)], np.float32) * 2.0 ** 21
-    else:
-        large = np.array([25, 19, 6, 1, 1], np.float32) * 2.0 ** 25
-    raw = np.zeros((n, d), np.float32)
-    for row in raw:
-        # near one another, in lanes that meet early, or anywhere
-        span = min(d, int(rng.choice([16, 64, 512, 2048, d])))
-        at = rng.integers(0, d - span + 1) + rng.choice(span, size=min(span, len(large) + 10), replace=False)
-        row[at[:len(large)]] = large
-        small = at[len(large):]
-        row[small] = rng.choice([5.5, 6.5, 7.75, 9.0, 11.0], len(small))
-    raw[::2] *= 2.0 ** rng.integers(-40, 5, (len(raw[::2]), 1))
-    return torch.from_numpy(raw).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
-
-
 @pytest.mark.parametrize("key_format", ["bf16", "fp8"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d", [100, 512, 1100, 2048, 4001, 4096, 5001, 5120, 6144, 8190, 8192])
@@ -164,7 +130,7 @@ def test_bulk_append_stores_the_same_bits(oil, key_format, dtype, d):
     append gives those of appends too small for the bulk kernel, for rows whose
     norm depends on the order of its sum."""
     n = 700
-    raw = _order_rows(n, d, dtype, seed=d)
+    raw = torch.from_numpy(order_rows(n, d, dtype, seed=d)).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
     raw[1::7] = torch.randn((len(raw[1::7]), d), generator=torch.Generator().manual_seed(d)).to(raw.dtype)
     raw = raw.cuda()
     ids = torch.arange(n, dtype=torch.int32).cuda()

@@ -13,7 +13,7 @@ import pytest
 import torch
 
 import oracle
-from tests._parity import TOL
+from tests._parity import TOL, order_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -90,8 +90,7 @@ def _check_ring(rp, recs_list, R, d):
     (300, [(2, 16, 65), (3, 16, 65), (4, 4, 17)], "bf16", 192),  # wraps around
     (100, [(5, 32, 65)], np.float32, 192),                    # one batch larger than the ring
     (64, [(6, 70, 9), (7, 1, 1)], np.float32, 192),           # 70 trees (two match groups); a root-only tree
-    # key rows of 1,536 and 4,096 columns: the normalising kernel's two wider
-    # branches (eight values per thread; the looping pass)
+    # key rows of several 8-column chunks per lane
     (400, [(8, 8, 33), (9, 4, 17)], np.float32, 1536),
     (400, [(10, 8, 33)], "bf16", 1536),
     (300, [(11, 8, 33), (12, 4, 17)], np.float32, 4096),
@@ -105,6 +104,56 @@ def test_insert_ring_bit_exact(oil, R, batches, dtype, d):
         _insert(oil, rp, bt)
         recs.append(_oracle_records(bt, d))
     _check_ring(rp, recs, R, d)
+
+
+def _unit_rows(raw):
+    """The bf16 bits of the unit rows of raw (n, d) float64, the squares summed as a
+    256-thread block sums them: thread t's columns t, t + 256, ... in order, lanes
+    32, 16, ... 1 apart, then the four waves."""
+    n, d = raw.shape
+    sq = np.zeros((n, (d + 255) // 256 * 256))
+    sq[:, :d] = raw * raw
+    sq = sq.reshape(n, -1, 4, 64)
+    s = sq[:, 0].copy()
+    for m in range(1, sq.shape[1]):
+        s += sq[:, m]
+    for o in (32, 16, 8, 4, 2, 1):
+        s = s + s[..., np.arange(64) ^ o]
+    s = s[..., 0]
+    norm = np.sqrt(((s[:, 0] + s[:, 1]) + s[:, 2]) + s[:, 3])
+    m, e = np.frexp(raw / np.where(norm > 0, norm, 1)[:, None])
+    q = np.ldexp(np.rint(m * 256) / 256, e).astype(np.float32)     # no quotient here is below the normal range
+    return (q.view(np.uint32) >> 16).astype(np.uint16)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, "bf16"])
+@pytest.mark.parametrize("d", [40, 191, 512, 2881, 4096, 5120, 8190, 8192, 8200])
+def test_insert_keys_keep_their_order_of_additions(oil, d, dtype):
+    """Record keys bit for bit, over the widths of the kernels (rows in pieces of 16
+    bytes or not, up to 4,096 and 8,192 columns, wider), for rows whose norm
+    depends on the order of its sum, ordinary ones, a zero row and rows of
+    extreme norm.  Chains of which nothing is accepted: every node but the last
+    is the key of one record."""
+    B, mx = 9, 33
+    raw = order_rows(B * mx, d, "f32" if dtype == np.float32 else "bf16", seed=d)
+    rng = np.random.default_rng(d)
+    raw[1::7] = rng.standard_normal(raw[1::7].shape)
+    raw[2] = 0
+    raw[3] = 1e30 * rng.standard_normal(d)
+    raw[4] = 1e-30 * rng.standard_normal(d)
+    states = torch.from_numpy(raw.reshape(B, mx, d))
+    if dtype == "bf16":
+        states = states.to(torch.bfloat16)
+    rp = oil.RecyclePool(d, B * (mx - 1) + 5)
+    par = np.tile(np.arange(-1, mx - 1, dtype=np.int32), (B, 1))
+    tok, tg = np.full((B, mx), 1, np.int32), np.full((B, mx), 2, np.int32)
+    rp.insert(_cu(tok), _cu(par), _cu(np.full(B, mx, np.int32)), _cu(tg), _cu(np.zeros(B, np.int32)),
+              _cu(np.full((B, mx), -1, np.int32)), states.cuda())
+    torch.cuda.synchronize()
+    want = _unit_rows(states[:, :-1].reshape(-1, d).double().numpy())
+    got = _bits(rp.keys)[:len(want)]
+    assert int(rp.head.cpu()[0]) == len(want)
+    assert np.array_equal(got[:, :d], want) and not got[:, d:].any()
 
 
 def test_lookup_matches_oracle(oil):
