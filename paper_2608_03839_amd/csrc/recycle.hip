@@ -492,7 +492,10 @@ hipError_t launch_recycle_insert(int32_t B, int32_t max_nodes, const int32_t* no
                            rec_slot, total, capacity, keys, head);
         return hipGetLastError();
     }
-    const bool f32 = dtype == 0, vec = ((int64_t)d * (f32 ? 4 : 2)) % 16 == 0, narrow = ld <= 4096;
+    // 16-byte pieces where every row starts on one; states at any other address
+    // (a slice of a larger tensor, say) are read element by element
+    const bool f32 = dtype == 0, narrow = ld <= 4096;
+    const bool vec = ((int64_t)d * (f32 ? 4 : 2)) % 16 == 0 && (uintptr_t)states % 16 == 0;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(most < 1 ? 1 : (most + 3) / 4)), dim3(256), 0, stream, states, d,
                            ld, rec_src, rec_slot, total, capacity, keys, head);

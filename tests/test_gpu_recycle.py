@@ -156,6 +156,26 @@ def test_insert_keys_keep_their_order_of_additions(oil, d, dtype):
     assert np.array_equal(got[:, :d], want) and not got[:, d:].any()
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [256, 4096, 5120])
+def test_insert_takes_states_at_any_element(oil, d, dtype):
+    """States that start at an element which is not 16-byte aligned, with rows whose
+    width is a multiple of 16 bytes: the keys of the aligned copy."""
+    bt = _batch(21, 4, 17, d)
+    src = torch.from_numpy(bt["states"]).to(dtype).cuda().reshape(-1)
+    room = torch.empty(src.numel() + 1, dtype=dtype, device="cuda")
+    room[1:] = src
+    keys = []
+    for st in (src, room[1:]):
+        rp = oil.RecyclePool(d, 100)
+        _insert(oil, rp, dict(bt, states=st.view(4, 17, d)))
+        torch.cuda.synchronize()
+        n = int(rp.head.cpu()[0])
+        keys.append(_bits(rp.keys)[:n])
+    assert room[1:].data_ptr() % 16 != 0 and n > 10
+    assert np.array_equal(*keys)
+
+
 def test_lookup_matches_oracle(oil):
     d, R = 256, 4096
     rp = oil.RecyclePool(d, R)
