@@ -263,12 +263,16 @@ __global__ __launch_bounds__(256) void scan_gemv_kernel(
     for (int b = 0; b < NB; b++)
         acc[b] = 0.f;
     for (; rb < n_rb; rb += stride) {
-        const int64_t next = rb + stride < n_rb ? rb + stride : rb;  // after the last row block: loads nobody uses
+        // after its last row block: loads nobody uses, of the window just read (its
+        // first windows again, long gone from the caches, cost short rows: 131,072 x
+        // 512, one query 38.2 -> 35.4 us)
+        const bool more = rb + stride < n_rb;
+        const int64_t next = more ? rb + stride : rb;
         for (int i0 = 0; i0 < nloop; i0 += NS) {
 #pragma unroll
             for (int u = 0; u < NS; u++) {
                 const int il = i0 + u + PF;
-                request(a[(u + PF) % NS], il < nloop ? rb : next, il < nloop ? il : il - nloop);
+                request(a[(u + PF) % NS], il < nloop ? rb : next, il < nloop || !more ? il : il - nloop);
                 const int w = SPLIT ? 4 * (i0 + u) + wave : i0 + u;
                 if (w < nwin) {
                     const int col = w * kWindow + 32 * h;
@@ -1537,9 +1541,13 @@ hipError_t launch_scan(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws,
     }
     if (!scan_uses_mfma(B, ld) && FS && (int64_t)B * n_valid <= kGemvScoresMax) {  // the GEMV scan only where it writes every score
         const bool split = n_rb <= 2 * (int64_t)device_cus();
+        // every wave as many row blocks, or one less, unless that leaves more than
+        // a quarter of the waves out: then all of them, some with a row block more.
+        // 4,096 wide, one query, us, equal shares / all waves: 2,188 row blocks (half
+        // the waves) 132 / 117, 4,219 (69%) 201 / 198, 3,125 (76%) 147 / 156
         const int64_t most = (int64_t)device_cus() * 4 * kGemvPerCu, rounds = (n_rb + most - 1) / most;
-        // every wave as many row blocks, or one less
-        const dim3 g((unsigned)(split ? n_rb : ((n_rb + rounds - 1) / rounds + 3) / 4));
+        const int64_t equal = (n_rb + rounds - 1) / rounds, waves = 4 * equal >= 3 * most ? equal : std::min(n_rb, most);
+        const dim3 g((unsigned)(split ? n_rb : (waves + 3) / 4));
         const size_t lds = (size_t)B * ld * sizeof(uint16_t);
         const uint16_t* q = (const uint16_t*)qbuf;
         switch (B) {
