@@ -1502,18 +1502,27 @@ static void launch_wide(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws
 //    chain of loads as long as a row) costs as much as the scan, the stores next
 //    to nothing: 8,000 x 4,096, 16 queries, k = 16: 24 us against under 1.  On
 //    larger pools the stores cost the scan more (128 MB at 1M positions: 200 us).
-//  * Above: where the stores cost less than the rescore.  4,096 wide, k = 16,
-//    whole call, us, rescored / with full scores: 128,000 positions, 100 / 200 /
-//    512 queries 262 / 391 / 804 against 225 / 289 / 551; 400,001 positions
-//    663 / 975 / 1,804 against 692 / 894 / 1,692; 800,000 positions 1,216 /
-//    1,777 / 3,254 against 1,449 / 1,749 / 3,402; fp8 keys, 400,001 positions
-//    390 / 600 / 1,087 against 416 / 592 / 1,056.  At most 512 MiB.
-int64_t scan_full_rows(int32_t B, int32_t k, int64_t row_bytes)
+//  * Above: up to where a call that rescores (only the blocks that can hold a
+//    second hit) takes as long.  That lies further out with k, which sets the
+//    selection from a second launch's candidates, and nearer for the widest
+//    batches, whose scans have the least bandwidth to spare; it moves little
+//    with the rows' width and format (1,024 to 8,192 columns) and not with how
+//    the queries' hits cluster.  Whole call with full scores, in shares of the
+//    rescored one (bf16, 4,096 wide; the rule's line between the columns | |):
+//      B, k      65,536  80,000  100,000  131,072  160,000  200,000  400,001
+//      100,  8    0.90    0.94 |  0.98     1.10     1.05     1.12     1.18
+//      200, 16    0.92    0.94    0.97  |  1.01     1.00     1.02     1.04
+//      256, 64    0.79    0.86    0.89     0.97     1.02     0.98  |
+//      300, 32    0.94    0.94    0.96     1.01  |  1.02     1.02
+//      512, 16    1.03 |  1.06    1.05     1.11     1.12     1.12     1.15
+//      512, 64    0.82    0.89    0.92     1.00  |  1.02     1.04     1.09
+//    At most 256 MiB, which holds the widest batches at k = 64 back a little (512
+//    queries, 1,024 wide, 160,000: 0.93).
+int64_t scan_full_rows(int32_t B, int32_t k)
 {
     if (B <= 64)
         return 2048 * kRowBlock;
-    const int64_t even = (int64_t)k * kRowBlock * row_bytes / (B <= 128 ? 14 : 5);
-    return std::max<int64_t>(1024 * kRowBlock, std::min<int64_t>(even, (1 << 27) / B) / 64 * 64);
+    return (int64_t)std::min(2560 - 5 * std::max(B - 256, 0) + 64 * k, (1 << 21) / B) * kRowBlock;
 }
 
 hipError_t launch_scan(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,
