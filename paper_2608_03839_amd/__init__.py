@@ -28,6 +28,7 @@ MAX_K, MAX_B, MAX_NODES, MAX_BANDS = 64, 512, 256, 4
 MAX_B_FP8 = 512
 LEX_MAX_CTX, LEX_MAX_N, LEX_MAX_LEN, LEX_MAX_CAND = 32, 16, 64, 4096
 LEX_MAX_HIST = 1 << 20
+SCORE_ROOM_MAX = 1 << 30
 REC_DEPTH, REC_MAX_OUT = 6, 8
 
 _lib = None
@@ -86,6 +87,7 @@ def lib():
             "oil_pool_size": (i32, [P, ctypes.POINTER(i64)]),
             "oil_pool_append": (i32, [P, P, i32, P, P, P, i64, P]),
             "oil_query_workspace_bytes": (sz, [P, i32, i32]),
+            "oil_query_workspace_least_bytes": (sz, [P, i32, i32]),
             "oil_pool_query_topk": (i32, [P, P, i32, i32, i32, P, P, sz, P, P, P]),
             "oil_pool_query_topk_noalloc": (i32, [P, P, i32, i32, i32, P, P, P, P]),
             "oil_gather_continuations": (i32, [P, P, P, i32, i32, ctypes.POINTER(DepthRule), i32,
@@ -188,6 +190,10 @@ def pool_append(handle, keys, tokens, trace_ids, prompt_ids=None, stream=None):
 
 def query_workspace_bytes(handle, B, k) -> int:
     return lib().oil_query_workspace_bytes(handle, B, k)
+
+
+def query_workspace_least_bytes(handle, B, k) -> int:
+    return lib().oil_query_workspace_least_bytes(handle, B, k)
 
 
 def pool_query_topk(handle, queries, k, workspace, scores, idx, exclude_prompt=None, stream=None):
@@ -355,6 +361,7 @@ class Pool:
         else:
             raise ValueError(f"key_format must be 'bf16' or 'fp8', got {key_format!r}")
         self._ws = {}
+        self._score_room = 0
 
     def __del__(self):
         h = getattr(self, "handle", None)
@@ -374,6 +381,12 @@ class Pool:
             nb = query_workspace_bytes(self.handle, B, k)
             if nb == 0:
                 raise ValueError(f"unsupported query batch/k: B={B} k={k}")
+            # workspaces are kept (captured graphs hold their addresses); what they
+            # hold beyond the least, room for every score, is bounded over all sizes
+            least = query_workspace_least_bytes(self.handle, B, k)
+            if self._score_room + nb - least > SCORE_ROOM_MAX:
+                nb = least
+            self._score_room += nb - least
             self._ws[key] = torch.empty((nb,), dtype=torch.uint8, device=self.device)
         return self._ws[key]
 

@@ -402,6 +402,13 @@ size_t oil_query_workspace_bytes(const oil_pool* pool, int32_t B, int32_t k)
     return carve(pool, B, k).total;
 }
 
+size_t oil_query_workspace_least_bytes(const oil_pool* pool, int32_t B, int32_t k)
+{
+    if (!pool || B < 1 || B > OIL_MAX_B || k < 1 || k > OIL_MAX_K)
+        return 0;
+    return carve(pool, B, k, false).total;
+}
+
 int32_t oil_pool_query_topk(const oil_pool* pool, const void* queries, int32_t q_dtype, int32_t B,
                             int32_t k, const int32_t* exclude_prompt, void* workspace,
                             size_t workspace_bytes, float* scores, int32_t* idx, void* stream)

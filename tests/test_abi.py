@@ -249,3 +249,26 @@ def test_scan_timer_rejects_bad_arguments(L):
     assert L.oil_scan_timer_start(4, -3) != 0
     n, ms = ctypes.c_int32(), ctypes.c_double()
     assert L.oil_scan_timer_stop(ctypes.byref(n), ctypes.byref(ms)) != 0   # never started
+
+
+def test_a_pool_keeps_little_room_for_scores(L):
+    """Workspaces of a store that is still small, over many batch sizes (as ragged
+    serving batches ask for): beyond the least each call needs, a Pool keeps at
+    most SCORE_ROOM_MAX bytes in all, and at most 256 MiB for any one."""
+    import paper_2608_03839_amd as oil
+    keys = ctypes.c_void_p(1 << 24)              # never dereferenced
+    pool = oil.Pool.__new__(oil.Pool)            # (the constructor's buffers are device memory)
+    pool.handle, pool.device = ctypes.c_void_p(), "cpu"
+    pool._ws, pool._score_room = {}, 0
+    assert L.oil_pool_create(64, 1 << 18, keys, keys, keys, None, ctypes.byref(pool.handle)) == 0
+    room = 0
+    for k in (8, 64):
+        for B in [*range(1, 128, 16), *range(129, 513, 13), 512]:
+            least = oil.query_workspace_least_bytes(pool.handle, B, k)
+            extra = pool.workspace(B, k).numel() - least
+            assert 0 <= extra <= 256 << 20
+            assert oil.query_workspace_bytes(pool.handle, B, k) - least <= 256 << 20
+            room += extra
+    assert 0 < room <= oil.SCORE_ROOM_MAX
+    assert L.oil_query_workspace_least_bytes(pool.handle, 513, 8) == 0
+    assert L.oil_query_workspace_least_bytes(pool.handle, 4, 65) == 0
