@@ -205,6 +205,74 @@ def test_topk_runs_of_neighbours(oil, key_format, B, k):
     check_topk(s_.cpu().numpy(), i_.cpu().numpy(), o, k)
 
 
+def _near_ties(n, seed, key_format):
+    """Raw rows (n, 64) f32, scores against (1, 1, 1, 1, 0, ...) known without
+    rounding: half of them from a few values around one level (steps of one ulp
+    for bf16 keys; E4M3 values, which are ties, for fp8), in blocks where one, a
+    few or all of the 32 rows lie there, the others far below."""
+    rng = np.random.default_rng(seed)
+    raw = np.zeros((n, 64))
+    blocks = -(-n // 32)
+    for b in range(blocks):
+        rows = np.arange(32 * b, min(n, 32 * b + 32))
+        top = rng.random(len(rows)) < rng.choice([0.0, 0.05, 0.3, 1.0], p=[0.5, 0.3, 0.15, 0.05])
+        # the level in parts that bf16 holds exactly: multiples of 2^-8, 2^-16 and 2^-24
+        step = rng.choice([0, 0, 1, 2, 31, 32, 33, 64], len(rows)) * rng.choice([0, 1], len(rows))
+        if key_format == "bf16":
+            raw[rows, 0] = np.where(top, 0.75, rng.integers(128, 160, len(rows)) / 256)
+            raw[rows, 1] = 2.0 ** -9
+            raw[rows, 2] = (128 + step) * 2.0 ** -24
+        else:
+            raw[rows, 0] = np.where(top, 0.75, rng.choice([0.5, 0.375, 0.25], len(rows)))
+        raw[rows, 5] = np.sqrt(1 - (raw[rows, :5] ** 2).sum(1))
+    return torch.from_numpy(raw.astype(np.float32))
+
+
+@pytest.mark.parametrize("key_format", ["bf16", "fp8"])
+@pytest.mark.parametrize("B", [8, 40, 100, 300])
+@pytest.mark.parametrize("k", [1, 5, 32, 64])
+def test_rescore_cut_at_near_ties(oil, key_format, B, k):
+    """Blocks whose best and second-best scores lie within a few ulps of the k-th
+    best score, equal ones among them (the same upper 27 bits, the same value, in
+    one block and in several), with exclusions that leave a block one row or none:
+    the exact top k, positions and score bits, with the chosen blocks rescored
+    and, where the call has room, with every score written.  The scores are sums
+    that fp32 holds exactly in any order."""
+    n = 5000 - 7 * k
+    raw = _near_ties(n, seed=B * 100 + k, key_format=key_format)
+    rng = np.random.default_rng(k)
+    prompts = rng.integers(0, B, n).astype(np.int32)
+    prompts[(np.arange(n) % 32 != 11) & (np.arange(n) // 32 % 5 < 2)] = B - 1
+    ids = torch.arange(n, dtype=torch.int32).cuda()
+    pool = oil.Pool(64, n, key_format=key_format)
+    pool.append(raw.cuda(), ids, ids, torch.from_numpy(prompts).cuda())
+    q = torch.zeros(B, 64)
+    q[:, :4] = 1
+    ex = np.arange(B, dtype=np.int32)
+    ex[::4] = -1
+    ex[B // 2:] = B - 1
+    out = []
+    for nb in {oil.query_workspace_least_bytes(pool.handle, B, k), oil.query_workspace_bytes(pool.handle, B, k)}:
+        s, i = torch.empty((B, k), device="cuda"), torch.empty((B, k), dtype=torch.int32, device="cuda")
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        oil.pool_query_topk(pool.handle, q.cuda(), k, ws, s, i, exclude_prompt=torch.from_numpy(ex).cuda())
+        out.append((s, i))
+    torch.cuda.synchronize()
+    assert len(out) == 2
+    if key_format == "bf16":
+        o = oracle_rows(_stored(pool, n), q.numpy(), prompts, ex)
+    else:
+        qc, qi = oracle.quantize_rows_fp8(q.numpy())
+        o = oracle.scores_fp8(untile_keys_fp8(pool.keys.cpu().numpy(), n, 64, pool.capacity),
+                              pool.scales[:n].cpu().numpy().astype(np.float64), qc, qi)
+        o[ex[:, None] == prompts[None, :]] = -np.inf
+    assert np.array_equal(o, o.astype(np.float32)) and len(np.unique(o)) > 4
+    best = np.argsort(-o, axis=1, kind="stable")[:, :k]
+    for s, i in out:
+        assert np.array_equal(i.cpu().numpy(), best)
+        assert np.array_equal(s.cpu().numpy(), np.take_along_axis(o, best, 1).astype(np.float32))
+
+
 @pytest.mark.parametrize("key_format,B,extra,d", [("bf16", 8, 1000, 64), ("bf16", 40, 1000, 64),
                                                    ("fp8", 8, 777, 64), ("fp8", 40, 4000, 64),
                                                    ("bf16", 16, 0, 64), ("bf16", 16, 100, 64),
@@ -903,8 +971,8 @@ def test_small_pool_kernels_agree(oil, key_format, B):
     """One capacity, pools cut at every size where the scan changes kernel: the
     top-k of each equals the best of its prefix by exact scores (the same
     selection rules as everywhere), with the queries' own prompts excluded, and
-    is bit-identical to the allocation-free call, whose scratch may hold no
-    full scores, so that the chosen blocks are rescored there."""
+    is bit-identical to a call on the least workspace (no full scores: the
+    chosen blocks are rescored) and to the allocation-free call."""
     d, k = 256, 24
     sizes = _small_pool_rows(B)
     n = sizes[-1]
@@ -921,8 +989,15 @@ def test_small_pool_kernels_agree(oil, key_format, B):
         s, i = pool.query_topk(q.cuda(), k, exclude_prompt=ex)
         s2, i2 = torch.empty_like(s), torch.empty_like(i)
         oil.pool_query_topk_noalloc(pool.handle, q.cuda(), k, s2, i2, exclude_prompt=ex)
+        nb, least = (f(pool.handle, B, k) for f in (oil.query_workspace_bytes, oil.query_workspace_least_bytes))
+        # the GEMV scan always writes every score, no pool past the limit has room for them
+        assert (least < nb) == ((B > 4 or key_format == "fp8") and not (B <= 64 and m > 2048 * 32))
+        s3, i3 = torch.empty_like(s), torch.empty_like(i)
+        ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+        oil.pool_query_topk(pool.handle, q.cuda(), k, ws, s3, i3, exclude_prompt=ex)
         torch.cuda.synchronize()
         assert torch.equal(i, i2) and torch.equal(s.view(torch.int32), s2.view(torch.int32))
+        assert torch.equal(i, i3) and torch.equal(s.view(torch.int32), s3.view(torch.int32))
         if key_format == "bf16":
             o = oracle_rows(_stored(pool, m), q.cpu().numpy(), prompts[:m].numpy(), ex.cpu().numpy())
         else:
