@@ -81,15 +81,15 @@ size_t topk_cand_bytes(int32_t B, int32_t k, int64_t capacity);
 hipError_t launch_topk_blocks(const uint64_t* G, int64_t g_ld, int64_t n_valid, int32_t B, int32_t k,
                               uint64_t* cand_a, uint64_t* cand_b, const uint64_t** chosen,
                               hipStream_t stream);
-// SC: the rescored scores (k * 32 per query), or, with full_scores set (the
-// GEMV scan's every score, fs_ld per query), the chosen blocks' rows read
-// from there.
 // Whether a pool of n_valid positions whose scan wrote every score is selected
 // from in one launch (launch_topk_scored: block keys and scores -> the ranked
 // top-k).
 bool topk_scored(int64_t n_valid);
 hipError_t launch_topk_scored(const uint64_t* G, int64_t g_ld, int64_t n_valid, int32_t B, int32_t k, float* out_s,
                               int32_t* out_i, hipStream_t stream, const float* full_scores, int64_t fs_ld);
+// SC: the rescored scores (k * 32 per query), or, with full_scores set (every
+// score, as the scan wrote them, fs_ld per query), the chosen blocks' rows read
+// from there.
 hipError_t launch_topk_final(const uint64_t* chosen, int32_t B, int32_t k, const float* SC,
                              int64_t n_valid, float* out_s, int32_t* out_i, hipStream_t stream,
                              const float* full_scores = nullptr, int64_t fs_ld = 0);

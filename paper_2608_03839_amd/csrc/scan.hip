@@ -5,9 +5,11 @@
 // best score and row, and a bound on its runner-up (block_word); the top-k
 // passes pick the k best blocks per query and the rescore kernel below
 // recomputes the 32 scores of those that can hold a second hit, with the
-// scan's own instruction sequence (bit-identical values).  Writing every
-// score (B x N x 4 bytes) interleaves a large store stream with the key reads
-// and costs far more than its bytes; re-reading k blocks per query does not.
+// scan's own instruction sequence (bit-identical values).  On large pools
+// writing every score (B x N x 4 bytes) interleaves a large store stream with
+// the key reads and costs far more than its bytes; re-reading k blocks per
+// query does not.  Small pools (scan_full_rows) have every score written and
+// nothing rescored.
 //
 // The pool is stored as 4 KiB tiles (32 rows x 64 columns) in MFMA operand
 // order, window-major (see store.hip): every 16-byte-per-lane load reads
@@ -1297,12 +1299,12 @@ static void launch_narrow(const uint16_t* keys, int32_t ld, int64_t rs, int64_t 
 {
     // Pools too small to give every SIMD a wave of MT row blocks: one row
     // block per workgroup of the remainder kernel up to two per compute unit,
-    // then one and two row blocks per wave up to one wave per SIMD.  4,096
-    // These write every score where the caller has room (FS).  4,096
-    // wide, 8 queries, us (bf16 keys, remainder kernel / 1 / 2 / 4 row blocks
-    // per wave): 250 row blocks 15 / 32 / 50 / 84; 500 29 / 35 / 54 / 89;
-    // 1,000 59 / 42 / 60 / 95; 2,000 132 / 82 / 77 / 105; 3,125 - / 141 / 137 /
-    // 123.  64 queries and fp8 keys change places at the same sizes.
+    // then one and two row blocks per wave up to one wave per SIMD.  These
+    // write every score where the caller has room (FS).  4,096 wide, 8 queries,
+    // us (bf16 keys, remainder kernel / 1 / 2 / 4 row blocks per wave): 250 row
+    // blocks 15 / 32 / 50 / 84; 500 29 / 35 / 54 / 89; 1,000 59 / 42 / 60 / 95;
+    // 2,000 132 / 82 / 77 / 105; 3,125 - / 141 / 137 / 123.  64 queries and fp8
+    // keys change places at the same sizes.
     const int64_t cus = device_cus();
     if (n_rb <= cus || (n_rb <= 2 * cus && ld * (FMT == kKeyBf16 ? 2 : 1) >= 1024)) {  // (short rows: 8.8 against 10)
         dispatch_n(sl, true, true, scan_tail_kernel<NT, FMT>, dim3((unsigned)n_rb), dim3(64 * (NT + 4)), 0, keys, ld,
@@ -1495,19 +1497,18 @@ static void launch_wide(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws
 
 // Positions up to which the MFMA scan of a batch writes every score, so that
 // the final selection reads the chosen blocks' scores instead of rescoring
-// them.  The scores are B n_valid 4 bytes, the rescored blocks B k 32
-// row_bytes; per byte the stores cost the HBM-bound scans more.
+// them.  The scores are B n_valid 4 bytes, the blocks rescored at most B k 32
+// rows; per byte the stores cost the HBM-bound scans more.
 //  * Up to 64 queries: the pools of the kernels above that take few row blocks
 //    per wave (16 MiB of scores at most).  There the rescore (B k waves, each a
 //    chain of loads as long as a row) costs as much as the scan, the stores next
 //    to nothing: 8,000 x 4,096, 16 queries, k = 16: 24 us against under 1.  On
 //    larger pools the stores cost the scan more (128 MB at 1M positions: 200 us).
 //  * Above: up to where a call that rescores (only the blocks that can hold a
-//    second hit) takes as long.  That lies further out with k, which sets the
-//    selection from a second launch's candidates, and nearer for the widest
-//    batches, whose scans have the least bandwidth to spare; it moves little
-//    with the rows' width and format (1,024 to 8,192 columns) and not with how
-//    the queries' hits cluster.  Whole call with full scores, in shares of the
+//    second hit) takes as long.  That lies further out with k, of which the
+//    rescore's launches and bytes are a multiple, and nearer for the widest
+//    batches, whose scans the stores slow most; it moves little with the rows'
+//    width and format (1,024 to 8,192 columns).  Whole call with full scores, in shares of the
 //    rescored one (bf16, 4,096 wide; the rule's line between the columns | |):
 //      B, k      65,536  80,000  100,000  131,072  160,000  200,000  400,001
 //      100,  8    0.90    0.94 |  0.98     1.10     1.05     1.12     1.18

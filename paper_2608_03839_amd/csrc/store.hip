@@ -271,8 +271,8 @@ __global__ __launch_bounds__(kRowThreads) void quantize_rows_kernel(
 // value through a division in double.)
 // The rows stay in registers between the norm and the rounding: memory is
 // read once and written once, which is what bounds it: 60,001 rows of 4,096
-// bf16 values into a bf16 pool 896 -> 201 us (4.9 TB/s in and out, a plain
-// copy's rate), 20,011 rows of 5,120 f32 values into an fp8 pool 331 -> 130.
+// bf16 values into a bf16 pool 896 -> 190 us (5.2 TB/s in and out), 20,011 rows
+// of 5,120 f32 values into an fp8 pool 331 -> 119 (4.3 TB/s).
 //
 // VEC: whole 16-byte pieces of every row are aligned (base and row stride);
 // other widths load element by element.
