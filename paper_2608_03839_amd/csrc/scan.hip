@@ -252,10 +252,19 @@ __global__ __launch_bounds__(256) void scan_gemv_kernel(
         for (int s = 0; s < 4; s++)
             dst[s] = __builtin_nontemporal_load(kv + at + s * 64);
     };
+    // The queries' first pieces are asked for before the keys: loads return in
+    // order, so a wait for queries behind the keys is a wait for the keys (32,768
+    // x 512, one / four queries 18.8 / 20.2 -> 18.3 / 19.5 us).
+    const int64_t j0 = threadIdx.x * 8, nj = (int64_t)NB * ld;
+    const int64_t jq = j0 < nj ? j0 : 0;  // (threads past the queries write the first piece too)
+    const bf16x8 q0 = *(const bf16x8*)(q + jq);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int p = 0; p < PF; p++)
         request(a[p], idle ? n_rb - 1 : rb, p);
-    for (int64_t j = threadIdx.x * 8; j < (int64_t)NB * ld; j += 256 * 8)
+    __builtin_amdgcn_sched_barrier(0);
+    *(bf16x8*)(q_lds + jq) = q0;
+    for (int64_t j = j0 + 256 * 8; j < nj; j += 256 * 8)
         *(bf16x8*)(q_lds + j) = *(const bf16x8*)(q + j);
     __syncthreads();
     if (idle)
