@@ -175,10 +175,14 @@ __device__ __forceinline__ double block_max(double m, double* red)
 // Power-of-two scale shift putting the row's largest magnitude m in [128, 256).
 __device__ __forceinline__ int fp8_shift(double m) { return m > 0.0 ? 7 - ilogb(m) : 0; }
 
-// Whether m is so near a power of two that the last bits of the norm decide it.
+// Whether m is so near a power of two (2^-40 of it, on either side) that the last
+// bits of the norm decide it: its mantissa is within 2^12 steps above zero, or
+// 2^13 below the next binade's.  (Working out both neighbours' exponents: 20,000
+// bf16 rows of 1,000 / 5,120 columns 22.0 / 61.8 us against 21.5 / 61.0.)
 __device__ __forceinline__ bool fp8_shift_near(double m)
 {
-    return fp8_shift(m * (1.0 + 0x1p-40)) != fp8_shift(m * (1.0 - 0x1p-40));
+    const uint64_t u = (uint64_t)__double_as_longlong(m) + (1u << 13);
+    return m > 0.0 && (u & ((1ull << 52) - 1)) <= 3u << 12;
 }
 
 // One row of quantize_rows_kernel for ld8 <= NT * NV, read once into
