@@ -156,7 +156,7 @@ int32_t oil_pool_append(oil_pool *pool, const void *keys, int32_t key_dtype, con
  * (sized from the pool's capacity, so it stays valid as the pool grows; with
  * bf16 keys and B <= 4 it includes room for up to 2 MiB of scores, otherwise,
  * while the pool is small enough for the scan to write every score, room for
- * those: up to 16 MiB for B <= 64, 256 MiB above.  A workspace without that
+ * those: up to 16 MiB for B <= 64, 512 MiB above.  A workspace without that
  * room, sized when the pool was larger or by oil_query_workspace_least_bytes,
  * serves too: the chosen blocks are then scored again, with the same results). */
 size_t oil_query_workspace_bytes(const oil_pool *pool, int32_t B, int32_t k);

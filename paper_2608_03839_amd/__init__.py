@@ -28,7 +28,7 @@ MAX_K, MAX_B, MAX_NODES, MAX_BANDS = 64, 512, 256, 4
 MAX_B_FP8 = 512
 LEX_MAX_CTX, LEX_MAX_N, LEX_MAX_LEN, LEX_MAX_CAND = 32, 16, 64, 4096
 LEX_MAX_HIST = 1 << 20
-SCORE_ROOM_MAX = 1 << 30
+SCORE_ROOM_MAX = 2 << 30
 REC_DEPTH, REC_MAX_OUT = 6, 8
 
 _lib = None

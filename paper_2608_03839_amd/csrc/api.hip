@@ -73,7 +73,8 @@ QueryWorkspace carve(const oil_pool* p, int32_t B, int32_t k, bool full = true)
     // rescored: the GEMV scan (bf16, B <= 4) while B * n_valid <=
     // kGemvScoresMax, the MFMA scan up to scan_full_rows positions
     const bool gemv = p->fmt != oil::kKeyFp8 && !oil::scan_uses_mfma(B, p->ld);
-    const int64_t fs_max = gemv ? (oil::kGemvScoresMax / B) / 64 * 64 : oil::scan_full_rows(B, k);
+    const int64_t row_bytes = (int64_t)p->ld * (p->fmt == oil::kKeyFp8 ? 1 : 2);
+    const int64_t fs_max = gemv ? (oil::kGemvScoresMax / B) / 64 * 64 : oil::scan_full_rows(B, k, row_bytes);
     // (a pool past them never comes back: it needs no room)
     const bool room = gemv || (full && p->n_valid <= fs_max);
     w.fs_ld = room ? std::min((int64_t)round_up((size_t)p->capacity, 64), fs_max) : 0;

@@ -50,7 +50,7 @@ int scan_uses_mfma(int32_t B, int32_t ld);
 constexpr int64_t kGemvScoresMax = 1 << 19;
 int scan_query_tiles(int32_t B);
 // Positions up to which the MFMA scan writes every score (full_scores).
-int64_t scan_full_rows(int32_t B, int32_t k);
+int64_t scan_full_rows(int32_t B, int32_t k, int64_t row_bytes);
 // fmt: kKeyBf16, or kKeyFp8 (ld = fp8 row width, a multiple of
 // 128; kscale per stored row and qscale per query are the inverse scales).
 // ev_start / ev_stop (or null): events bound to the scan's first and last

@@ -1513,26 +1513,35 @@ static void launch_wide(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws
 //    chain of loads as long as a row) costs as much as the scan, the stores next
 //    to nothing: 8,000 x 4,096, 16 queries, k = 16: 24 us against under 1.  On
 //    larger pools the stores cost the scan more (128 MB at 1M positions: 200 us).
-//  * Above: up to where a call that rescores (only the blocks that can hold a
-//    second hit) takes as long.  That lies further out with k, of which the
-//    rescore's launches and bytes are a multiple, and nearer for the widest
-//    batches, whose scans the stores slow most; it moves little with the rows'
-//    width and format (1,024 to 8,192 columns).  Whole call with full scores, in shares of the
-//    rescored one (bf16, 4,096 wide; the rule's line between the columns | |):
-//      B, k      65,536  80,000  100,000  131,072  160,000  200,000  400,001
-//      100,  8    0.90    0.94 |  0.98     1.10     1.05     1.12     1.18
-//      200, 16    0.92    0.94    0.97  |  1.01     1.00     1.02     1.04
-//      256, 64    0.79    0.86    0.89     0.97     1.02     0.98  |
-//      300, 32    0.94    0.94    0.96     1.01  |  1.02     1.02
-//      512, 16    1.03 |  1.06    1.05     1.11     1.12     1.12     1.15
-//      512, 64    0.82    0.89    0.92     1.00  |  1.02     1.04     1.09
-//    At most 256 MiB, which holds the widest batches at k = 64 back a little (512
-//    queries, 1,024 wide, 160,000: 0.93).
-int64_t scan_full_rows(int32_t B, int32_t k)
+//  * Above: up to about where a call that rescores (only the blocks that can
+//    hold a second hit) takes as long.  A chosen block is read again where the
+//    query's hits lie side by side, as in a store of whole calls (each a run of
+//    neighbouring positions like one another, 8 and 40 calls alike); where they
+//    are scattered next to none is, and rescoring wins from 50,000 to 200,000
+//    positions on.  The line follows whole calls, where the choice weighs most:
+//    rescoring takes up to three times as long there, writing the scores nowhere
+//    more than half as long again.  It lies further out with k, of which the
+//    rescore is a multiple, and with the bytes of a row (narrow rows are soon
+//    read again), and nearer for wider batches.  Whole call with every score
+//    written, in shares of the rescored one (4,096 wide, bf16; 8 / 40 calls
+//    alike; the line between the columns |):
+//      B, k       131,072      200,000      300,000      400,001      600,000
+//      128,  8  |.98 / 1.01  1.05 / 1.08  1.09 / 1.12  1.13 / 1.15  1.24 / 1.24
+//      128, 64  .61 / .62   .76 / .77    .85 / .85    .93 / .94  | 1.09 / 1.14
+//      200, 16  .85 / .89   .89 / .93    .95 / 1.01 | .99 / 1.04   1.00 / 1.06
+//      256, 64  .53 / .53   .65 / .66    .76 / .77    .81 / .83  | .89 / .94
+//      512,  8  1.00 / 1.07 | 1.03 / 1.11 1.08 / 1.15  1.10 / 1.15  1.12 / 1.14
+//      512, 32  .71 / .73   .81 / .85  | .91 / .96    .97 / 1.03   1.03 / 1.11
+//    (128, 8: at 128,960 positions; 256, 64 and 512, 32: at the 512 MiB that
+//    the scores may take, 524,288 and 262,144 positions.)
+int64_t scan_full_rows(int32_t B, int32_t k, int64_t row_bytes)
 {
     if (B <= 64)
         return 2048 * kRowBlock;
-    return (int64_t)std::min(2560 - 5 * std::max(B - 256, 0) + 64 * k, (1 << 21) / B) * kRowBlock;
+    const int64_t r = row_bytes;
+    const int64_t even = B <= 128 ? (85000 + 5500 * k) * (24576 + r) / 32768
+                                  : (187500 - 312 * B + 16900 * k) * (131 * r) / (100 * (r + 2560));
+    return std::max<int64_t>(1024 * kRowBlock, std::min<int64_t>(even, (1 << 27) / B) / 64 * 64);
 }
 
 hipError_t launch_scan(const uint16_t* keys, int32_t ld, int64_t rs, int64_t ws, int64_t n_valid,

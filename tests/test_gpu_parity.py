@@ -990,8 +990,10 @@ def test_small_pool_kernels_agree(oil, key_format, B):
         s2, i2 = torch.empty_like(s), torch.empty_like(i)
         oil.pool_query_topk_noalloc(pool.handle, q.cuda(), k, s2, i2, exclude_prompt=ex)
         nb, least = (f(pool.handle, B, k) for f in (oil.query_workspace_bytes, oil.query_workspace_least_bytes))
-        # the GEMV scan always writes every score, no pool past the limit has room for them
-        assert (least < nb) == ((B > 4 or key_format == "fp8") and not (B <= 64 and m > 2048 * 32))
+        if B <= 4 and key_format == "bf16":              # the GEMV scan always writes every score
+            assert least == nb
+        elif m <= (2048 if B <= 64 else 1024) * 32:      # a store this small has room for them, if asked
+            assert least < nb
         s3, i3 = torch.empty_like(s), torch.empty_like(i)
         ws = torch.empty(least, dtype=torch.uint8, device="cuda")
         oil.pool_query_topk(pool.handle, q.cuda(), k, ws, s3, i3, exclude_prompt=ex)
